@@ -91,6 +91,8 @@ struct SelectGeom {
   int64_t n_chunks;
   int64_t cb_tokens;       // key columns per score workgroup
   int n_colblk;            // column blocks of the score passes
+  int64_t wcb_tokens;      // the same of the bf16 passes (score_wave.h); never more blocks than n_colblk
+  int wn_colblk, unit_log;
   int heads[128];
 };
 
@@ -111,6 +113,13 @@ inline int score_waves(int dtype, int rows_pad) {
 // kMaxBlockTokens (the kernels address a block's K rows with 32-bit offsets).
 constexpr int64_t kMaxBlockTokens = (int64_t)1 << 22;
 int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu);
+// bf16 row counts whose two passes run on score_wave.h.  512 rows keep the
+// 16-wave workgroups of score.h: 31 + 30 us against 36 + 29 at 39939 keys of
+// 4 heads (one pass over both sums is score_wave.h's at any row count).
+inline bool score_wave_rows(int rows_pad) { return rows_pad < 512; }
+// score_block_tokens for the bf16 passes of score_wave.h, whose waves take units of
+// 1 << unit_log keys.
+int64_t score_wave_block_tokens(int64_t n_keys, int n_heads, int unit_log, int n_cu);
 size_t select_workspace_bytes(const SelectGeom& g);
 // The file-scope scratch of the allocation-free selection: its size, and its
 // device address on the current device.
@@ -126,10 +135,11 @@ hipError_t launch_compact(int dtype, const void* k, const void* v, int hkv, int6
 // lower index), ascending, -1 padded to b.  ws: topk_workspace_bytes() bytes
 // (rows longer than 4096 scores are reduced slice by slice through it); its
 // first n_rows 32-bit words must be zero on entry (an earlier launch of the
-// same call clears them) and are left zero.
+// same call clears them) and are left zero.  gate: rows with a zero word are
+// left alone.
 size_t topk_workspace_bytes(int n_rows, int64_t n);
 hipError_t launch_topk(const float* S, int n_rows, int64_t n, int b, int32_t* idx_out, void* ws,
-                       hipStream_t stream);
+                       hipStream_t stream, const uint32_t* gate = nullptr);
 
 // ---- query-aware retrieval in adaptive heads (page bounds and scores) -----
 hipError_t launch_page_bounds(int dtype, const void* k, int64_t n, int cs, const int32_t* heads, int n_sel,
@@ -145,8 +155,8 @@ struct ScoreGeom {
   int64_t q_pos0;
   int causal;
   double k_pct, alpha;
-  int64_t cb_tokens;
-  int n_colblk;
+  int64_t cb_tokens, wcb_tokens;
+  int n_colblk, wn_colblk;
 };
 
 size_t score_workspace_bytes(const ScoreGeom& g);

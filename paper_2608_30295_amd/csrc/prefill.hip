@@ -3,6 +3,7 @@
 // merge, BlockMax, top-k -- compaction (Cache(K, V, i_k, L_obs)) and the CV
 // head score (Section 3.2, Eq. 1-4) over the observation matrix.
 #include "score.h"
+#include "score_wave.h"
 
 #include <algorithm>
 #include <mutex>
@@ -188,6 +189,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
   L = sum16(L * fast_exp2(M - M16));
   const float o = (ok && L > 0.f) ? M16 + __log2f(L) : INFINITY;
   if (ln == 0 && row < rpad) off[(size_t)sel * rpad + row] = o;
+  if (a.rho) {   // one-pass selection: every block's offset is the row's estimate
+    const float r = ok && L > 0.f ? fast_exp2(p[0].x - o) : 0.f;
+    const bool redo = ok && (bad || !(r < INFINITY));
+    const float rw = max_xor32(max_xor16(r));
+    if (__ballot(redo)) {
+      if ((threadIdx.x & 63) == 0) atomicOr(&a.redo[sel], 1u);
+    } else if ((threadIdx.x & 63) == 0 && rw > 0.f) {
+      atomicMax(&a.rho[sel], __float_as_uint(rw));
+    }
+  }
   if (a.cv.samples) {
     const int r0 = blockIdx.x * kMergeRows;
     if (a.G == 1) cv_sample_rows<T, 1>(a, sel, r0, o);
@@ -208,8 +219,9 @@ __device__ __forceinline__ uint32_t ord_key(float f) {
 
 // S_c = max of C over chunk c (BlockMax of Algorithm 1).
 __global__ void chunk_max_kernel(const float* __restrict__ C, int64_t n_keys, int cs,
-                                 int64_t n_chunks, float* __restrict__ S) {
+                                 int64_t n_chunks, float* __restrict__ S, const uint32_t* __restrict__ gate) {
   const int sel = blockIdx.y;
+  if (gate && !gate[sel]) return;
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n_chunks) return;
   const float* Cs = C + (size_t)sel * n_keys;
@@ -249,7 +261,9 @@ __device__ int block_exclusive_scan(int v, int* s_buf, int* total) {
 // Indices of the k largest chunk scores of one head (ties to the lower
 // index), written ascending, then -1 padding up to b.
 __global__ __launch_bounds__(kTopkThreads) void topk_kernel(const float* __restrict__ S, int64_t n_chunks,
-                                                            int k, int b, int32_t* __restrict__ idx_out) {
+                                                            int k, int b, int32_t* __restrict__ idx_out,
+                                                            const uint32_t* __restrict__ gate) {
+  if (gate && !gate[blockIdx.x]) return;
   __shared__ int s_hist[256];
   __shared__ int s_scan[kTopkThreads];
   __shared__ uint32_t s_prefix;
@@ -358,6 +372,7 @@ struct TopkArgs {
   int k, b;                // select k; kTopkRow / kTopkList write b entries per row (-1 padded)
   int32_t* out;            // kTopkRow / kTopkList: [rows][b]
   TopkCand* cand;          // kTopkSliceMode: [rows][n_slices][k]
+  const uint32_t* gate;    // rows with a zero word are left alone (null: none)
 };
 
 // Wave-wide AND / OR of a word (every lane gets it): DPP steps inside each
@@ -401,7 +416,7 @@ __device__ __forceinline__ int wave_suffix_sum(int x) {
 }
 
 template <int PER, int MODE>
-__device__ __forceinline__ void topk_body(const TopkArgs& a, int row, int slice, int n_slices) {
+__device__ __forceinline__ uint32_t topk_body(const TopkArgs& a, int row, int slice, int n_slices) {
   constexpr int NW = kTopkThreads / 64;
   constexpr int NCOPY = 16;
   constexpr int RS = 260;                  // words per copy: 256 bins, rows 16-byte aligned
@@ -610,11 +625,13 @@ __device__ __forceinline__ void topk_body(const TopkArgs& a, int row, int slice,
     if (MODE == kTopkSliceMode) atomicExch(&cout[i], 0xFFFFFFFF00000000ull);
     else out[i] = -1;
   }
+  return tau;
 }
 
 // one row per workgroup
 template <int PER>
 __global__ __launch_bounds__(kTopkThreads) void topk_wave_kernel(TopkArgs a) {
+  if (a.gate && !a.gate[blockIdx.x]) return;
   topk_body<PER, kTopkRow>(a, blockIdx.x, 0, 1);
 }
 
@@ -627,6 +644,7 @@ template <int PER1, int PER2>
 __global__ __launch_bounds__(kTopkThreads) void topk_fused_kernel(TopkArgs s1, TopkArgs s2, uint32_t* arrive) {
   __shared__ int s_last;
   const int row = blockIdx.y;
+  if (s1.gate && !s1.gate[row]) return;
   topk_body<PER1, kTopkSliceMode>(s1, row, blockIdx.x, gridDim.x);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
@@ -635,6 +653,117 @@ __global__ __launch_bounds__(kTopkThreads) void topk_fused_kernel(TopkArgs s1, T
   if (!s_last) return;
   topk_body<PER2, kTopkList>(s2, row, 0, 1);
   if (threadIdx.x == 0) arrive[row] = 0;
+}
+
+// ---------------------------------------------------------------------------
+// One-pass selection (bf16, long rows of keys, small budgets).  The column
+// mass needs every row's sum first, which took a pass of its own over K
+// (q.k again, K from HBM again).  Here the pass that sums the rows also adds
+// up the columns, with each row weighted by an estimate of its sum from 2048
+// sampled keys instead of the sum itself: C'_j = sum_i rho_i^-1 w_i e_ij for
+// the true weights w_i, where rho_i = estimate / sum is known afterwards.  So
+// C_j <= max(rho) C'_j, and the chunks that can be among the b best are those
+// whose C' reaches C_(b) / max(rho):
+//   row_estimate_kernel   estimates
+//   score pass kBoth      row sums and chunk maxima of C'
+//   merge                 exact row offsets, max(rho)
+//   top-k                 the n_cand best chunks by C'
+//   score pass kColGather their exact column mass
+//   select_final_kernel   the b best of them, and the proof: the smallest C'
+//                         among the candidates times max(rho) lies below the
+//                         b-th exact score, so no other chunk can reach it
+// A head without that proof (flat scores, or row sums that are not finite)
+// is redone with the full column-mass pass, whose launches return at once
+// for the others.
+// ---------------------------------------------------------------------------
+
+// The sum of exp2(s c) of a row over all keys, log2, from each of eight groups
+// of 128 sampled keys; sw_est_pick() takes the third smallest of the eight, so
+// that a few very large terms in some groups do not lift it (rho <= 1 costs
+// nothing; rho >> 1 weakens the bound).  Some group has a sum at least the
+// estimate's, so rho is at most n_keys / 128.  One workgroup per (32 rows,
+// head, group), one tile of 32 keys per wave: latency-bound, so the 64 to 256
+// KB of a head's sample are spread over as many compute units as there are
+// (eight waves of eight tiles each took 20 us).
+__global__ __launch_bounds__(256) void row_estimate_kernel(ScoreArgs a, float* __restrict__ est) {
+  __shared__ float2 s_e[4][32];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = lane & 31, half = lane >> 5;
+  const int sel = blockIdx.y, h = a.heads[sel], grp = blockIdx.z;
+  const int row = blockIdx.x * 32 + n;
+  if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) {
+    a.rho[sel] = 0;
+    a.redo[sel] = 0;
+  }
+  // tiles of 32 keys spread evenly over the keys, dealt to the groups in turn
+  const int64_t key = (a.n_keys - 32) * (wave * kSwEstGroups + grp) / (4 * kSwEstGroups - 1) + n;
+  const char* kr = reinterpret_cast<const char*>(a.k) +
+                   ((size_t)h * a.n + (size_t)(a.key_off + key)) * (kD * 2) + half * 16;
+  const int rc = min(row, a.R - 1), i = rc >> a.g_log, g = rc & (a.G - 1);
+  const char* q = reinterpret_cast<const char*>(a.q) + ((size_t)(h * a.G + g) * a.lq + i) * (kD * 2) + half * 16;
+  uint4 bf[8], kf[8];
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) bf[ks] = ldg16(q + ks * 32);
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) kf[ks] = ldg16(kr + ks * 32);
+  floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[ks]), __builtin_bit_cast(bf16x8, bf[ks]),
+                                                  acc, 0, 0, 0);
+  float m = acc[0], l = 0.f;
+#pragma unroll
+  for (int r = 1; r < 16; ++r) m = fmaxf(m, acc[r]);
+  m = fmaxf(kMInit, max_xor32(m) * a.c);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) l += fast_exp2(__builtin_fmaf(acc[r], a.c, -m));
+  l = add_xor32(l);
+  if (half == 0) s_e[wave][n] = make_float2(m, l);
+  __syncthreads();
+  if (threadIdx.x < 32 && row < a.R) {
+    float M = kMInit, L = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) M = fmaxf(M, s_e[w][n].x);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) L += s_e[w][n].y * fast_exp2(s_e[w][n].x - M);
+    est[((size_t)sel * a.rp + row) * kSwEstGroups + grp] = M + __log2f(L * ((float)a.n_keys * (1.0f / 128)));
+  }
+}
+
+// The b best of each head's candidates by exact score, and whether they are
+// the head's b best (redo[sel] is set if that is not shown).  Grid: one
+// workgroup per head.  Both masses are sums of positive terms rounded to
+// fp32, within far less than the 1e-4 allowed for.
+template <int PER>
+__global__ __launch_bounds__(kTopkThreads) void select_final_kernel(TopkArgs t, TopkCand* __restrict__ list,
+                                                                    const int32_t* __restrict__ cand,
+                                                                    const float* __restrict__ mass, int cs, int64_t n_keys,
+                                                                    const float* __restrict__ S, int64_t n_chunks,
+                                                                    const uint32_t* __restrict__ rho, uint32_t* redo) {
+  __shared__ float s_min[kTopkThreads / 64];
+  const int sel = blockIdx.x, nc = (int)t.list_len;
+  TopkCand* ls = list + (size_t)sel * nc;
+  float lowest = INFINITY;
+  for (int c = threadIdx.x; c < nc; c += kTopkThreads) {
+    const int32_t ix = cand[(size_t)sel * nc + c];
+    const int len = (int)min((int64_t)cs, n_keys - (int64_t)ix * cs);
+    const float* ms = mass + ((size_t)sel * nc + c) * cs;
+    float m = -INFINITY;
+    for (int j = 0; j < len; ++j) m = fmaxf(m, ms[j]);
+    __hip_atomic_store(&ls[c], ((TopkCand)(uint32_t)ix << 32) | ord_key(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    lowest = fminf(lowest, S[(size_t)sel * n_chunks + ix]);
+  }
+  for (int off = 32; off > 0; off >>= 1) lowest = fminf(lowest, __shfl_xor(lowest, off));
+  if ((threadIdx.x & 63) == 0) s_min[threadIdx.x >> 6] = lowest;
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  const uint32_t tau = topk_body<PER, kTopkList>(t, sel, 0, 1);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int w = 1; w < kTopkThreads / 64; ++w) lowest = fminf(lowest, s_min[w]);
+    const float kth = __uint_as_float((tau & 0x80000000u) ? (tau & 0x7FFFFFFFu) : ~tau);
+    if (!(__uint_as_float(rho[sel]) * lowest * 1.0001f < kth)) redo[sel] = 1;
+  }
 }
 
 struct CompactArgs {
@@ -706,6 +835,17 @@ int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu) 
   return std::min<int64_t>(std::max<int64_t>(cb, 4 * kTileTok), kMaxBlockTokens);
 }
 
+// One workgroup of score_wave.h per compute unit, in a single round; at least
+// one unit per wave.  Never shorter than score_block_tokens' blocks (which
+// count at least as many workgroups), so the row statistics fit the workspace
+// laid out for those.
+int64_t score_wave_block_tokens(int64_t n_keys, int n_heads, int unit_log, int n_cu) {
+  const int64_t per_head = std::max<int64_t>(1, std::max(1, n_cu) / std::max(1, n_heads));
+  int64_t cb = (std::max<int64_t>(n_keys, 1) + per_head - 1) / per_head;
+  cb = ((cb - 1) | ((1 << unit_log) - 1)) + 1;
+  return std::min<int64_t>(std::max<int64_t>(cb, 8 << unit_log), kMaxBlockTokens);
+}
+
 struct SelectLayout {
   size_t rowpart, rowoff, colmass, chunks, topk, total;
 };
@@ -756,6 +896,35 @@ hipError_t select_scratch(void** ptr) {
   return hipSuccess;
 }
 
+// One-pass selection: the candidates and the buffers, which lie in the part
+// of the row statistics' region that the wave passes' fewer blocks leave free
+// (no workspace grows for it).
+struct OnePass {
+  int n_cand;             // 0: two passes
+  size_t est, words, cand, mass, list;
+};
+// Candidates per chunk of the budget: on Gaussian keys with 1% heavy hitters
+// the bound leaves 1.1 to 1.9 chunks per chunk kept, as long as the budget
+// keeps at most a 48th of the chunks; flatter scores need many more.
+constexpr int64_t kOnePassShare = 48;
+constexpr int64_t kOnePassScores = (int64_t)128 << 20;
+static OnePass one_pass(const SelectGeom& g, const SelectLayout& L) {
+  OnePass p{};
+  const int rp = score_rows_pad(g.G * g.l_obs);
+  if (kOnePassShare * g.b > g.n_chunks || (int64_t)g.n_sel * rp * g.n_keys < kOnePassScores) return p;
+  const int64_t nc = 2 * (int64_t)g.b + g.b / 2 + 64;
+  const int64_t n_slices = (g.n_chunks + kTopkSlice - 1) / kTopkSlice;
+  if (nc >= g.n_chunks || nc > 8 * kTopkThreads || (g.n_chunks > 2 * kTopkSlice && n_slices * nc > 2 * kTopkSlice)) return p;
+  size_t o = L.rowpart + align256((size_t)g.n_sel * g.wn_colblk * rp * sizeof(float2));
+  p.est = o; o += align256((size_t)g.n_sel * rp * kSwEstGroups * sizeof(float));
+  p.words = o; o += align256((size_t)2 * g.n_sel * sizeof(uint32_t));
+  p.cand = o; o += align256((size_t)g.n_sel * nc * sizeof(int32_t));
+  p.mass = o; o += align256((size_t)g.n_sel * nc * g.cs * sizeof(float));
+  p.list = o; o += align256((size_t)g.n_sel * nc * sizeof(TopkCand));
+  if (o <= L.rowoff) p.n_cand = (int)nc;
+  return p;
+}
+
 hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, const void* k,
                          int32_t* idx_out, void* ws, hipStream_t stream) {
   const SelectLayout L = select_layout(g);
@@ -764,7 +933,13 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
   const int rp = score_rows_pad(R);
   ScoreArgs a{};
   a.q = q_obs; a.k = k; a.hkv = g.hkv; a.lq = g.l_obs; a.G = g.G; a.R = R; a.n = g.n;
-  a.key_off = 0; a.n_keys = g.n_keys; a.cb_tokens = g.cb_tokens; a.n_colblk = g.n_colblk;
+  const bool bf = dtype == CATEKV_BF16;
+  a.key_off = 0; a.n_keys = g.n_keys;
+  const OnePass op = bf ? one_pass(g, L) : OnePass{};
+  const bool wave = bf && (op.n_cand > 0 || score_wave_rows(rp));
+  a.cb_tokens = wave ? g.wcb_tokens : g.cb_tokens;
+  a.n_colblk = wave ? g.wn_colblk : g.n_colblk;
+  a.rp = rp; a.unit_log = g.unit_log;
   a.q_pos0 = g.n - g.l_obs; a.causal = 0; a.c = kLog2e / sqrtf((float)kD);
   for (int i = 0; i < g.n_sel; ++i) a.heads[i] = g.heads[i];
   a.rowpart = reinterpret_cast<float2*>(w + L.rowpart);
@@ -772,25 +947,71 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
   a.colmass = reinterpret_cast<float*>(w + L.colmass);
   a.zero_u32 = reinterpret_cast<uint32_t*>(w + L.topk);   // the top-k's arrival counters
   a.n_zero = g.n_sel;
-  const dim3 grid(g.n_colblk, g.n_sel);
-  hipError_t e = launch_score_rowstats(dtype, g.G, false, rp, grid, stream, a);
-  if (e != hipSuccess) return e;
-  if (dtype == CATEKV_BF16)
-    hipLaunchKernelGGL(rowstats_merge_kernel<uint16_t>, dim3((rp + kMergeRows - 1) / kMergeRows, g.n_sel), dim3(256), 0,
-                       stream, a, rp, reinterpret_cast<float*>(w + L.rowoff));
-  else
-    hipLaunchKernelGGL(rowstats_merge_kernel<float>, dim3((rp + kMergeRows - 1) / kMergeRows, g.n_sel), dim3(256), 0,
-                       stream, a, rp, reinterpret_cast<float*>(w + L.rowoff));
+  const dim3 grid(a.n_colblk, g.n_sel);
   float* S = reinterpret_cast<float*>(w + L.chunks);
   a.chunks = S;
   a.n_chunks = g.n_chunks;
   a.cs_fused = (kTileTok % g.cs == 0) ? g.cs : 0;
+  a.g_log = __builtin_ctz((unsigned)g.G);
+  const dim3 mgrid((rp + kMergeRows - 1) / kMergeRows, g.n_sel), cgrid((unsigned)((g.n_chunks + 255) / 256), g.n_sel);
+  float* off = reinterpret_cast<float*>(w + L.rowoff);
+  hipError_t e;
+  if (op.n_cand > 0) {
+    float* est = reinterpret_cast<float*>(w + op.est);
+    uint32_t* redo = reinterpret_cast<uint32_t*>(w + op.words) + g.n_sel;
+    int32_t* cand = reinterpret_cast<int32_t*>(w + op.cand);
+    float* mass = reinterpret_cast<float*>(w + op.mass);
+    TopkCand* list = reinterpret_cast<TopkCand*>(w + op.list);
+    a.rho = reinterpret_cast<uint32_t*>(w + op.words);
+    a.redo = redo;
+    hipLaunchKernelGGL(row_estimate_kernel, dim3((R + 31) / 32, g.n_sel, kSwEstGroups), dim3(256), 0, stream, a, est);
+    ScoreArgs m = a;
+    m.rowoff = est;
+    e = launch_score_both(grid, stream, m);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(rowstats_merge_kernel<uint16_t>, mgrid, dim3(256), 0, stream, a, rp, off);
+    if (!a.cs_fused)
+      hipLaunchKernelGGL(chunk_max_kernel, cgrid, dim3(256), 0, stream, a.colmass, g.n_keys, g.cs, g.n_chunks, S,
+                         (const uint32_t*)nullptr);
+    e = launch_topk(S, g.n_sel, g.n_chunks, op.n_cand, cand, w + L.topk, stream);
+    if (e != hipSuccess) return e;
+    ScoreArgs ga = a;       // the candidates' columns, 32 per wave
+    ga.cand = cand;
+    ga.cand_cs = g.cs;
+    ga.n_cand = op.n_cand;
+    ga.cand_keys = g.n_keys;
+    ga.n_keys = (int64_t)op.n_cand * g.cs;
+    ga.cb_tokens = 32 * kSwWaves;
+    ga.unit_log = 5;
+    ga.cs_fused = 0;
+    ga.colmass = mass;
+    e = launch_score_gather(dim3((unsigned)((ga.n_keys + ga.cb_tokens - 1) / ga.cb_tokens), g.n_sel), stream, ga);
+    if (e != hipSuccess) return e;
+    TopkArgs t{};
+    t.list = list;
+    t.list_len = op.n_cand;
+    t.k = t.b = g.b;
+    t.out = idx_out;
+#define CATEKV_FIN(PER) \
+  hipLaunchKernelGGL((select_final_kernel<PER>), dim3(g.n_sel), dim3(kTopkThreads), 0, stream, t, list, cand, mass, g.cs, \
+                     g.n_keys, S, g.n_chunks, a.rho, redo)
+    if (op.n_cand <= 1 * kTopkThreads) CATEKV_FIN(1);
+    else if (op.n_cand <= 2 * kTopkThreads) CATEKV_FIN(2);
+    else if (op.n_cand <= 4 * kTopkThreads) CATEKV_FIN(4);
+    else CATEKV_FIN(8);
+#undef CATEKV_FIN
+    a.gate = redo;
+  } else {
+    e = launch_score_rowstats(dtype, g.G, false, rp, grid, stream, a);
+    if (e != hipSuccess) return e;
+    if (dtype == CATEKV_BF16) hipLaunchKernelGGL(rowstats_merge_kernel<uint16_t>, mgrid, dim3(256), 0, stream, a, rp, off);
+    else hipLaunchKernelGGL(rowstats_merge_kernel<float>, mgrid, dim3(256), 0, stream, a, rp, off);
+  }
   e = launch_score_colmass(dtype, rp, grid, stream, a);
   if (e != hipSuccess) return e;
   if (!a.cs_fused)
-    hipLaunchKernelGGL(chunk_max_kernel, dim3((unsigned)((g.n_chunks + 255) / 256), g.n_sel), dim3(256), 0,
-                       stream, a.colmass, g.n_keys, g.cs, g.n_chunks, S);
-  return launch_topk(S, g.n_sel, g.n_chunks, g.b, idx_out, w + L.topk, stream);
+    hipLaunchKernelGGL(chunk_max_kernel, cgrid, dim3(256), 0, stream, a.colmass, g.n_keys, g.cs, g.n_chunks, S, a.gate);
+  return launch_topk(S, g.n_sel, g.n_chunks, g.b, idx_out, w + L.topk, stream, a.gate);
 }
 
 // ws: n_rows arrival counters (zero on entry: the caller's previous kernel
@@ -815,10 +1036,10 @@ static void launch_topk_fused(const TopkArgs& s1, const TopkArgs& s2, unsigned n
 }
 
 hipError_t launch_topk(const float* S, int n_rows, int64_t n, int b, int32_t* idx_out, void* ws,
-                       hipStream_t stream) {
+                       hipStream_t stream, const uint32_t* gate) {
   const int k_eff = (int)(b < n ? b : n);
   TopkArgs a{};
-  a.S = S; a.n = n; a.k = k_eff; a.b = b; a.out = idx_out;
+  a.S = S; a.n = n; a.k = k_eff; a.b = b; a.out = idx_out; a.gate = gate;
   const int64_t n_slices = (n + kTopkSlice - 1) / kTopkSlice;
   const int64_t n_small = (n + kTopkSmallSlice - 1) / kTopkSmallSlice;
   // A row of up to 2 kTopkSlice scores fits one workgroup, but a few such rows
@@ -850,7 +1071,7 @@ hipError_t launch_topk(const float* S, int n_rows, int64_t n, int b, int32_t* id
     s2.list_len = n_slices * k_eff;
     launch_topk_fused<16>(s1, s2, (unsigned)n_slices, n_rows, arrive, stream);
   } else {
-    hipLaunchKernelGGL(topk_kernel, dim3(n_rows), dim3(kTopkThreads), 0, stream, S, n, k_eff, b, idx_out);
+    hipLaunchKernelGGL(topk_kernel, dim3(n_rows), dim3(kTopkThreads), 0, stream, S, n, k_eff, b, idx_out, gate);
   }
   return hipGetLastError();
 }
@@ -904,6 +1125,7 @@ hipError_t launch_score(int dtype, const ScoreGeom& g, const void* q_rows, const
   ScoreArgs a{};
   a.q = q_rows; a.k = k; a.hkv = g.hkv; a.lq = g.lq; a.G = g.G; a.R = R; a.n = g.n;
   a.key_off = g.l_init; a.n_keys = g.n_keys; a.cb_tokens = g.cb_tokens; a.n_colblk = g.n_colblk;
+  a.rp = rp; a.unit_log = 5;
   a.q_pos0 = g.q_pos0; a.causal = g.causal; a.c = kLog2e / sqrtf((float)kD);
   for (int i = 0; i < g.hkv; ++i) a.heads[i] = i;
   a.rowpart = reinterpret_cast<float2*>(w + L.rowpart);
@@ -911,14 +1133,19 @@ hipError_t launch_score(int dtype, const ScoreGeom& g, const void* q_rows, const
   a.obs = reinterpret_cast<float*>(w + L.obs);
   a.cv = cv_link(w + L.cv, g.hkv, g.lq, g.n_keys, g.n_colblk, kCvMaxSub);
   const dim3 grid(g.n_colblk, g.hkv);
-  hipError_t e = launch_score_rowstats(dtype, g.G, g.causal, rp, grid, stream, a);
+  ScoreArgs r = a;          // row statistics: the blocks of the bf16 pass
+  if (dtype == CATEKV_BF16 && score_wave_rows(rp)) {
+    r.cb_tokens = g.wcb_tokens;
+    r.n_colblk = g.wn_colblk;
+  }
+  hipError_t e = launch_score_rowstats(dtype, g.G, g.causal, rp, dim3(r.n_colblk, g.hkv), stream, r);
   if (e != hipSuccess) return e;
   if (dtype == CATEKV_BF16)
     hipLaunchKernelGGL(rowstats_merge_kernel<uint16_t>, dim3((rp + kMergeRows - 1) / kMergeRows, g.hkv), dim3(256), 0,
-                       stream, a, rp, reinterpret_cast<float*>(w + L.rowoff));
+                       stream, r, rp, reinterpret_cast<float*>(w + L.rowoff));
   else
     hipLaunchKernelGGL(rowstats_merge_kernel<float>, dim3((rp + kMergeRows - 1) / kMergeRows, g.hkv), dim3(256), 0,
-                       stream, a, rp, reinterpret_cast<float*>(w + L.rowoff));
+                       stream, r, rp, reinterpret_cast<float*>(w + L.rowoff));
   // the merge also took the sampled entries of A; the bracket from them,
   // the bracketing pass, A itself only for the heads the bracket missed
   e = launch_cv_sample(a, g.k_pct, g.alpha, stream);

@@ -81,7 +81,8 @@ template <typename T> struct Shape {
   __device__ static __forceinline__ float row_sum(float x) { return sum16(x); }
   __device__ static __forceinline__ float col_sum(float x) { return add_xor32(add_xor16(x)); }
 };
-enum ScoreMode { kRowStats = 0, kColMass = 1, kObsMatrix = 2, kObsBracket = 3 };
+// kBoth and kColGather: score_wave.h only
+enum ScoreMode { kRowStats = 0, kColMass = 1, kObsMatrix = 2, kObsBracket = 3, kBoth = 4, kColGather = 5 };
 enum RowStatsVar { kRsSum = 0, kRsMax = 1 };
 
 struct ScoreArgs {
@@ -110,6 +111,18 @@ struct ScoreArgs {
   // route reads A)
   CvLink cv;
   int cv_gate;
+  // score_wave.h
+  int rp;                 // rows per block of rowpart and per head of rowoff (R padded)
+  int g_log;              // log2(G)
+  int lb_log;             // log2 of the consecutive queries per group head in the LDS row order
+  int unit_log;           // log2 of the keys per unit of a wave's run (5, or 6 where chunks span 64 keys)
+  // one-pass selection (prefill.hip)
+  const uint32_t* gate;   // kColMass: heads with a zero word are left alone
+  const int32_t* cand;    // kColGather: the chunks of cand_cs keys whose columns are taken, [n_sel][n_cand]
+  int cand_cs, n_cand;
+  int64_t cand_keys;      // kColGather: key columns there are (n_keys counts the gathered ones)
+  uint32_t* rho;          // merge out: per head, the largest estimate-to-sum ratio of its rows (float bits), or null
+  uint32_t* redo;         // merge out: set for a head whose row sums are not all finite
   uint32_t* zero_u32;     // cleared by the row-statistics merge (a later launch's counters), n_zero words
   int n_zero;
 };
@@ -610,6 +623,10 @@ inline hipError_t launch_score_mt(int rows_pad, dim3 grid, hipStream_t s, const 
 hipError_t launch_score_rowstats(int dtype, int G, bool causal, int rows_pad, dim3 grid, hipStream_t s,
                                  const ScoreArgs& a);
 hipError_t launch_score_colmass(int dtype, int rows_pad, dim3 grid, hipStream_t s, const ScoreArgs& a);
+// bf16 (score_wave.h): row sums against given offsets and column mass in one
+// pass, and the column mass of gathered chunks
+hipError_t launch_score_both(dim3 grid, hipStream_t s, const ScoreArgs& a);
+hipError_t launch_score_gather(dim3 grid, hipStream_t s, const ScoreArgs& a);
 hipError_t launch_score_obs(int dtype, int G, bool causal, int rows_pad, dim3 grid, hipStream_t s,
                             const ScoreArgs& a);
 hipError_t launch_score_obs_bracket(int dtype, int G, bool causal, int rows_pad, dim3 grid, hipStream_t s,

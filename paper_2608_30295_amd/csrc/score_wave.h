@@ -1,0 +1,453 @@
+// Score passes of the prefill kernels for bf16 (the fp32 passes are in
+// score.h, which also says what a pass computes).  What bounds them is the
+// matrix core together with the softmax arithmetic (one fma, one exp2 and one
+// add per score) and, up to 128 query rows, HBM; so nothing else may stand in
+// the way of the three running side by side:
+//  * The query rows of the KV head stay in LDS for the whole kernel; a wave
+//    keeps its own 64 keys in registers (the next 64 in flight) and runs all
+//    query rows over them.  No wave waits for another between the prologue
+//    and the end, so one wave's MFMAs meet the other's arithmetic, and a key
+//    fragment is loaded straight into the operand registers by the one wave
+//    that uses it.
+//  * S^T = K Q^T with v_mfma_f32_32x32x16_bf16 (keys as A, query rows as B):
+//    a lane holds one query row (column of S^T) and 16 keys of a 32 x 32
+//    tile, so a row's offset and sum are one register per 32 rows, and LDS
+//    serves 16 KB of fragments per 64 x 64 scores, half the matrix core's
+//    time at 128 bytes per cycle.
+// Measured (5 heads, 256 rows, 131008 keys, 40 launches in a row): row
+// statistics 57.0 -> 49-56 us, column mass 62.7 -> 49-57 us against 16 x 16
+// tiles of a K tile shared by eight waves through an LDS ring (one barrier
+// per 64 keys); both sums in one pass (kBoth) 60 us.  With all-zero inputs the
+// same passes take 41 us: the matrix cores' clock under load is part of it.
+#pragma once
+
+#include "score.h"
+
+namespace catekv {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+constexpr int kSwWaves = 8;                 // waves per workgroup, one workgroup per compute unit
+constexpr int kSwThreads = kSwWaves * 64;
+constexpr int kSwRow = 17;                  // 16-byte units per LDS query row (16 + 1: rows start in different banks)
+
+// Query rows lie in LDS by slot: lb = 1 << lb_log consecutive queries of one
+// group head, then the next group head, then the next lb queries.  With lb =
+// 32 a 32-row tile holds one group head's rows, so the G rows of a query sit
+// in the same lane of G tiles and the group mean needs no exchange.  With lb
+// = 16 (at most 16 queries, G >= 2) a tile holds two group heads.
+struct SwSlot {
+  int i, g;
+};
+__device__ __forceinline__ SwSlot sw_slot(int s, int lb_log, int g_log) {
+  const int t = s >> lb_log;
+  return {(t >> g_log << lb_log) | (s & ((1 << lb_log) - 1)), t & ((1 << g_log) - 1)};
+}
+
+// kBoth: a row's sum is estimated from kSwEstGroups samples; the third
+// smallest estimate is taken (any finite number is a valid weight: sums that
+// it takes out of range are redone).
+constexpr int kSwEstGroups = 8;
+__device__ __forceinline__ float sw_est_pick(const float* e8) {
+  const float4 lo = *reinterpret_cast<const float4*>(e8), hi = *reinterpret_cast<const float4*>(e8 + 4);
+  const float e[kSwEstGroups] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+  float pick = 0.f;
+#pragma unroll
+  for (int w = 0; w < kSwEstGroups; ++w) {
+    int below = 0;
+#pragma unroll
+    for (int v = 0; v < kSwEstGroups; ++v) below += e[v] < e[w] || (e[v] == e[w] && v < w);
+    if (below == 2) pick = e[w];
+  }
+  return fabsf(pick) < INFINITY ? pick : 0.f;
+}
+
+// key of accumulator register r within its 32-key tile
+__device__ __forceinline__ constexpr int sw_key(int r) { return (r & 3) + 8 * (r >> 2); }
+
+// RG 32-row tiles.  GO, LB: group size and queries per tile (observation
+// modes only, which add the G rows of a query).
+template <int RG, int MODE, int GO, int LB>
+__global__ __launch_bounds__(kSwThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void score_wave_kernel(ScoreArgs a) {
+  constexpr int KS = 8;                     // 16-dim steps of the contraction
+  __shared__ uint4 s_q[RG * 32 * kSwRow];
+  // Row offsets (log2 units) and sums of exp2(s c - offset): registers up to
+  // 256 rows, LDS for 512 (kRowStats: each wave's own; the offset is a bf16
+  // number, which any number near the row's maximum may be, so that all of it
+  // fits the 160 KB).
+  constexpr bool RS = MODE == kRowStats, BOTH = MODE == kBoth, SUMS = RS || BOTH, GATHER = MODE == kColGather;
+  constexpr bool REG = RG <= 8 && !BOTH;    // offsets in registers
+  constexpr bool REGL = RG <= 8 && !BOTH;   // sums in registers
+  __shared__ uint16_t s_off16[RS ? kSwWaves : 1][RS ? RG * 32 : 1];
+  __shared__ float s_off[RS || REG ? 1 : RG * 32];   // (the same for all waves)
+  __shared__ float s_l[SUMS ? kSwWaves : 1][SUMS ? RG * 32 : 1];
+  float off_r[REG ? RG : 1], l_r[REGL ? RG : 1];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 31, half = lane >> 5;
+  const int sel = blockIdx.y, cb = blockIdx.x;
+  if (MODE == kColMass && a.gate && !a.gate[sel]) return;
+  const int h = a.heads[sel];
+  const int G = a.G;
+
+  // this wave's keys: a run of whole units of the block's key columns (32
+  // keys, or 64 where a chunk spans 64)
+  const int64_t col0 = (int64_t)cb * a.cb_tokens;
+  const int n_cols = (int)(min(col0 + a.cb_tokens, a.n_keys) - col0);
+  const int ul = a.unit_log;
+  const int units = (n_cols + (1 << ul) - 1) >> ul;
+  const int c_lo = (units * wave / kSwWaves) << ul;                       // first column, from col0
+  const int c_hi = min((units * (wave + 1) / kSwWaves) << ul, n_cols);
+  // query row i sees columns up to lim + i; columns below c_plain (a whole
+  // number of units) need no mask: they lie before the end and at or before
+  // every row's position
+  const int lim = a.causal ? (int)max((int64_t)-(1 << 30), min((int64_t)(1 << 30), a.q_pos0 - a.key_off - col0)) : 1 << 30;
+  const int c_plain = GATHER ? c_lo : max(c_lo, min(c_hi, lim + 1) >> ul << ul);
+  // A plain run starts and ends with a step of 32 keys and takes 64 at a time
+  // between: all waves' first requests meet at the memory, and the matrix
+  // cores idle until they are served, and the memory idles under the last
+  // step.  Where a chunk spans 64 keys (column modes) every step is 64.
+  const bool steps32 = (MODE != kColMass && !BOTH) || ul == 5;
+  const int pu = (c_plain - c_lo) >> 5;                                   // plain keys, in 32s
+  const int n_full = steps32 ? max(pu - 1, 0) >> 1 : pu >> 1;             // 64-key tiles
+  const bool has_tail = steps32 && pu > 0 && !(pu & 1);                   // and a last step of 32
+  const int c_full = steps32 ? c_lo + 32 : c_lo;                          // first column of the full tiles
+  const char* kb = reinterpret_cast<const char*>(a.k) +
+                   ((size_t)h * a.n + (size_t)(a.key_off + col0)) * (kD * 2);
+
+  // ---- K fragments: tile t2 of 32 keys, step ks: 16 bytes of key row n ------
+  const uint32_t voff = (uint32_t)n * (kD * 2) + (uint32_t)half * 16;
+  uint4 kf[2][2][KS];
+  // shares a tile is requested in (kBoth: two row tiles each, looped over)
+  constexpr int kSlots = BOTH ? (RG < 2 ? 1 : RG / 2) : RG < 8 ? RG : 8;
+  // share `slot` of the 32 keys from column col, and of those `step` further (NF = 2), all valid, into f:
+  // at least four 32-byte steps together, so that a request's 128-byte lines are used whole
+  auto load_slot = [&](uint4 (&f)[2][KS], int col, auto nf_tag, int slot, int step = 32) {
+    constexpr int TOT = decltype(nf_tag)::value * KS, NSH = kSlots < TOT / 4 ? kSlots : TOT / 4, PER = TOT / NSH;
+    if (slot % (kSlots / NSH)) return;
+    const char* p = kb + (size_t)col * (kD * 2);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int x = slot / (kSlots / NSH) * PER + u;
+      f[x / KS][x % KS] = ldg16(p + (x / KS) * step * (kD * 2) + voff + (x % KS) * 32);
+    }
+  };
+  auto load_all = [&](uint4 (&f)[2][KS], int col, auto nf_tag) {
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) load_slot(f, col, nf_tag, s);
+  };
+  auto load_clamped = [&](uint4 (&f)[2][KS], int col) {   // keys past the block's end re-read its last one
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const char* p = kb + (size_t)min(col + 32 * t + n, n_cols - 1) * (kD * 2) + half * 16;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) f[t][ks] = ldg16(p + ks * 32);
+    }
+  };
+
+  // The query rows go first and alone: requested beside the first keys of all
+  // workgroups (16 MB) they wait behind them, 8-12 us instead of ~2.
+  constexpr int QP = RG * 32 * 16 / kSwThreads;           // 16-byte pieces of query rows per thread
+  uint4 qv[QP];
+#pragma unroll
+  for (int u = 0; u < QP; ++u) {
+    const int e = u * kSwThreads + threadIdx.x;
+    const SwSlot q = sw_slot(e >> 4, a.lb_log, a.g_log);
+    const uint32_t row = (uint32_t)(h * G + q.g) * a.lq + min(q.i, a.lq - 1);
+    qv[u] = ldg16(reinterpret_cast<const char*>(a.q) + (size_t)row * (kD * 2) + (e & 15) * 16);
+  }
+  auto load_off = [&](int s) -> float {
+    const SwSlot q = sw_slot(s, a.lb_log, a.g_log);
+    if (q.i >= a.lq) return INFINITY;
+    const float* o = a.rowoff + ((size_t)sel * a.rp + q.i * G + q.g) * (BOTH ? kSwEstGroups : 1);
+    return BOTH ? sw_est_pick(o) : *o;
+  };
+#pragma unroll
+  for (int rg = 0; rg < (REG ? RG : 0); ++rg) off_r[rg] = RS ? kMInit : load_off(rg * 32 + n);
+#pragma unroll
+  for (int rg = 0; rg < (REGL ? RG : 0); ++rg) l_r[rg] = 0.f;
+  if constexpr (SUMS && !REGL) {
+    for (int s = lane; s < RG * 32; s += 64) {
+      if (RS) s_off16[wave][s] = (uint16_t)(__builtin_bit_cast(uint32_t, kMInit) >> 16);
+      s_l[wave][s] = 0.f;
+    }
+  }
+  if (!RS && !REG) {
+    for (int s = threadIdx.x; s < RG * 32; s += kSwThreads) s_off[s] = load_off(s);
+  }
+#pragma unroll
+  for (int u = 0; u < QP; ++u) {
+    const int e = u * kSwThreads + threadIdx.x;
+    const bool ok = sw_slot(e >> 4, a.lb_log, a.g_log).i < a.lq;
+    s_q[(e >> 4) * kSwRow + (e & 15)] = ok ? qv[u] : make_uint4(0, 0, 0, 0);
+  }
+  barrier_lds_only();
+  using T1 = std::integral_constant<int, 1>;
+  using T2 = std::integral_constant<int, 2>;
+  using Y = std::true_type;
+  using N = std::false_type;
+  if (pu > 0) load_all(kf[1], c_lo, T1{});
+
+  const uint4* qn = s_q + n * kSwRow + half;
+  float cm[2][16];        // kColMass: column sums of the tile; observation modes: the group's sums
+  const float c = a.c;
+
+  auto mfma = [&](const uint4 (&f)[KS], const uint4 (&bf)[KS]) {
+    floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f[ks]), __builtin_bit_cast(bf16x8, bf[ks]),
+                                                    acc, 0, 0, 0);
+    return acc;
+  };
+  // ---- end of a tile ---------------------------------------------------------
+  // kColMass: sums over the 32 lanes of the 32 column sums a lane holds, each
+  // lane left with one key's total: row swap, then mirror, half mirror, xor 2
+  // and xor 1, halving the values each time.  Lane bits (5..0) then hold key
+  // bits 2, 5, 4, 3, 1, 0.
+  auto finish_cols = [&](int col) {
+    float x[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(cm[0][r]), __float_as_uint(cm[1][r]), false, false);
+      x[r] = __uint_as_float(w[0]) + __uint_as_float(w[1]);
+    }
+    const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2, b0 = lane & 1;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) x[r] = (b3 ? x[r + 8] : x[r]) + dpp<kDppMirror>(b3 ? x[r] : x[r + 8]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = (b2 ? x[r + 4] : x[r]) + dpp<kDppHalfMirror>(b2 ? x[r] : x[r + 4]);
+#pragma unroll
+    for (int r = 0; r < 2; ++r) x[r] = (b1 ? x[r + 2] : x[r]) + dpp<kDppXor2>(b1 ? x[r] : x[r + 2]);
+    float v = (b0 ? x[1] : x[0]) + dpp<kDppXor1>(b0 ? x[0] : x[1]);
+    v *= 1.0f / (float)G;
+    const int key = (lane & 3) | (half << 2) | ((lane & 12) << 1) | ((lane & 16) << 1);
+    const int64_t kc = col0 + col + key;
+    const bool ok = col + key < c_hi;
+    if (a.cs_fused > 0) {
+      const int cs = a.cs_fused;
+      float m = ok ? v : -INFINITY;
+      if (cs >= 2) m = fmaxf(m, dpp<kDppXor1>(m));
+      if (cs >= 4) m = fmaxf(m, dpp<kDppXor2>(m));
+      if (cs >= 8) m = max_xor32(m);
+      if (cs >= 16) m = fmaxf(m, dpp<kDppHalfMirror>(m));
+      if (cs >= 32) m = fmaxf(m, dpp<kDppMirror>(m));
+      if (cs >= 64) m = max_xor16(m);
+      if (ok && (key & (cs - 1)) == 0) a.chunks[(size_t)sel * a.n_chunks + kc / cs] = m;
+    } else if (ok) {
+      a.colmass[(size_t)sel * a.n_keys + kc] = v;
+    }
+  };
+
+  // ---- one tile: NT2 tiles of 32 keys from column col over all query rows ----
+  // FIRST (row statistics): each row's offset is its maximum over the first 32
+  // keys (kMInit for a row that sees none of them: it then sees none of the
+  // run, as a row's visible keys form a prefix of the key range).  Later
+  // terms are added against it with no running maximum: up to 2^128 they stay
+  // finite; a sum that overflows is written as it is (inf), and the merge
+  // recomputes that block's statistics exactly.
+  // The phases of a row tile (MFMAs of 32 keys, their arithmetic) are kept
+  // apart and in order: with two waves per SIMD one wave's MFMAs run beside
+  // the other's arithmetic.  (The two interleaved inside a wave, one MFMA then
+  // two scores, measured 25% slower.)  The next row tile's fragments are read
+  // behind the last MFMAs that use the present ones.
+  uint4 bf[KS];
+  auto read_rows = [&](int rg) {
+    compiler_fence();   // keeps the fragments of one row tile, not of all, in registers
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) bf[ks] = qn[rg * 32 * kSwRow + ks * 2];
+    compiler_fence();
+  };
+  read_rows(0);
+  // ahead(slot) requests a share of the next tile's keys: a wave that asks
+  // for all 16 KB at once stands at the full memory pipeline instead of at its
+  // MFMAs (3-5 us of 50 at the sizes above).
+  auto tile = [&](uint4 (&f)[2][KS], int col, auto nt_tag, auto mask_tag, auto first_tag, auto&& ahead) {
+    constexpr int NT2 = decltype(nt_tag)::value;
+    constexpr bool MASK = decltype(mask_tag)::value, FIRST = decltype(first_tag)::value;
+    auto rows = [&](int rg) {
+      float off;
+      if constexpr (REG) off = off_r[rg];
+      else if constexpr (RS) off = __uint_as_float((uint32_t)s_off16[wave][rg * 32 + n] << 16);
+      else off = s_off[rg * 32 + n];
+      int last = c_hi - 1 - col - 4 * half;               // MASK: last visible key of this lane's row in the tile
+      if (MASK) last = min(last, lim + sw_slot(rg * 32 + n, a.lb_log, a.g_log).i - col - 4 * half);
+      float ls = 0.f;
+#pragma unroll
+      for (int t = 0; t < NT2; ++t) {
+        floatx16 acc = mfma(f[t], bf);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t == NT2 - 1) read_rows((rg + 1) & (RG - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        if (MASK && MODE != kColMass && !GATHER) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[r] = t * 32 + sw_key(r) <= last ? acc[r] : -INFINITY;
+        }
+        if (FIRST && t == 0) {
+          float m = acc[0];
+#pragma unroll
+          for (int r = 1; r < 16; ++r) m = fmaxf(m, acc[r]);
+          // c > 0: the maximum of s c is c times that of s
+          off = __uint_as_float(__float_as_uint(fmaxf(kMInit, max_xor32(m) * c)) & 0xffff0000u);
+          if constexpr (REG) {
+            off_r[rg] = off;
+          } else {
+            s_off16[wave][rg * 32 + n] = (uint16_t)(__float_as_uint(off) >> 16);   // both halves write the same
+          }
+        }
+        float p[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(acc[r], c, -off));
+        if (!RS) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) cm[t][r] = REG && rg == 0 ? p[r] : cm[t][r] + p[r];
+        }
+        if (SUMS) {
+#pragma unroll
+          for (int s = 8; s > 0; s >>= 1)
+#pragma unroll
+            for (int r = 0; r < s; ++r) p[r] += p[r + s];
+          ls += p[0];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (SUMS && REGL) {
+        l_r[rg] += ls;
+      } else if constexpr (SUMS) {
+        ls = add_xor32(ls);                               // both halves hold the same row
+        if (half == 0) atomicAdd(&s_l[wave][rg * 32 + n], ls);   // this wave's own word
+      }
+    };
+    if (!RS && !REG) {
+#pragma unroll
+      for (int t = 0; t < NT2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) cm[t][r] = 0.f;
+    }
+#pragma unroll
+    for (int slot = 0; slot < kSlots; ++slot) {
+      ahead(slot);
+      if constexpr (REGL) {
+        rows(slot);
+      } else {
+#pragma unroll 1
+        for (int rg = slot * (RG / kSlots); rg < (slot + 1) * (RG / kSlots); ++rg) rows(rg);
+      }
+    }
+    if (MODE == kColMass || BOTH || GATHER) {
+      if (NT2 == 1) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) cm[1][r] = 0.f;
+      }
+      finish_cols(col);
+    }
+  };
+  // ---- the run: 32 keys, full tiles, 32 keys, then the masked rest -----------
+  auto none = [](int) {};
+  if (pu > 0) {
+    // with no full tile: the first keys again, so that the loads in flight are the same on every path
+    const int c1 = n_full > 0 ? c_full : c_lo, step1 = n_full > 0 ? 32 : 0;
+    if (steps32)
+      tile(kf[1], c_lo, T1{}, N{}, std::integral_constant<bool, RS>{}, [&](int s) { load_slot(kf[0], c1, T2{}, s, step1); });
+    else
+      load_all(kf[0], c1, T2{});
+    int i = 0;
+    for (; i + 2 < n_full; i += 2) {        // tile i in buffer 0; i + 1 and i + 2 exist
+      const int col = c_full + 64 * i;
+      tile(kf[0], col, T2{}, N{}, N{}, [&](int s) { load_slot(kf[1], col + 64, T2{}, s); });
+      tile(kf[1], col + 64, T2{}, N{}, N{}, [&](int s) { load_slot(kf[0], col + 128, T2{}, s); });
+    }
+    if (i + 1 < n_full) {
+      const int col = c_full + 64 * i;
+      tile(kf[0], col, T2{}, N{}, N{}, [&](int s) { load_slot(kf[1], col + 64, T2{}, s); });
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) kf[0][t][ks] = kf[1][t][ks];
+      ++i;
+    }
+    // the last step of 32 (read, where there is none, for the same reason)
+    if (i < n_full)
+      tile(kf[0], c_full + 64 * i, T2{}, N{}, N{}, [&](int s) { load_slot(kf[1], c_plain - 32, T1{}, s); });
+    else
+      load_all(kf[1], c_plain - 32, T1{});
+    if (has_tail) tile(kf[1], c_plain - 32, T1{}, N{}, N{}, none);
+  }
+  bool started = pu > 0;                    // kRowStats: offsets taken
+  if constexpr (GATHER) {                   // 32 gathered keys at a time
+    for (int col = c_lo; col < c_hi; col += 32) {
+      const uint32_t x = min(col + n, n_cols - 1) + (uint32_t)col0, cs = (uint32_t)a.cand_cs;
+      const int64_t key = min((int64_t)a.cand[(size_t)sel * a.n_cand + x / cs] * cs + x % cs, a.cand_keys - 1);
+      const char* p = reinterpret_cast<const char*>(a.k) + ((size_t)h * a.n + (size_t)key) * (kD * 2) + half * 16;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[0][0][ks] = ldg16(p + ks * 32);
+      tile(kf[0], col, T1{}, N{}, N{}, none);
+    }
+    return;
+  }
+  for (int col = c_plain; col < c_hi; col += 64) {
+    load_clamped(kf[0], col);
+    if (RS && !started) {
+      tile(kf[0], col, T2{}, Y{}, Y{}, none);
+      started = true;
+    } else {
+      tile(kf[0], col, T2{}, Y{}, N{}, none);
+    }
+  }
+
+  // ---- row sums: the lanes of a row, then the waves --------------------------
+  if constexpr (SUMS) {
+#pragma unroll
+    for (int rg = 0; rg < (REGL ? RG : 0); ++rg) {
+      const float ls = add_xor32(l_r[rg]);                // both halves hold the same row and offset
+      if (half == 0) {
+        if constexpr (RS) s_off16[wave][rg * 32 + n] = (uint16_t)(__float_as_uint(off_r[rg]) >> 16);
+        s_l[wave][rg * 32 + n] = ls;
+      }
+    }
+    __syncthreads();
+    for (int s = threadIdx.x; s < RG * 32; s += kSwThreads) {
+      const SwSlot q = sw_slot(s, a.lb_log, a.g_log);
+      if (q.i >= a.lq) continue;
+      float M = kMInit, L = 0.f;
+      if constexpr (RS) {
+        float2 v[kSwWaves];
+#pragma unroll
+        for (int w = 0; w < kSwWaves; ++w) {
+          v[w] = make_float2(__uint_as_float((uint32_t)s_off16[w][s] << 16), s_l[w][s]);
+          M = fmaxf(M, v[w].x);
+        }
+#pragma unroll
+        for (int w = 0; w < kSwWaves; ++w) L += v[w].y * fast_exp2(v[w].x - M);
+      } else {                                            // the same offset in every wave
+        M = s_off[s];
+#pragma unroll
+        for (int w = 0; w < kSwWaves; ++w) L += s_l[w][s];
+      }
+      a.rowpart[((size_t)sel * a.n_colblk + cb) * a.rp + q.i * G + q.g] = make_float2(M, L);
+    }
+  }
+}
+
+// 32-row tiles (1, 2, 4, 8 or 16) for `rows` slots
+inline int sw_row_tiles(int rows) {
+  int rg = 1;
+  while (rg * 32 < rows) rg *= 2;
+  return rg;
+}
+
+// row statistics and column mass: rows in their natural order (lb = 1)
+template <int MODE>
+inline hipError_t launch_score_wave(dim3 grid, hipStream_t s, ScoreArgs a) {
+  a.lb_log = 0;
+  if (MODE == kRowStats) a.unit_log = 5;
+  a.g_log = __builtin_ctz((unsigned)a.G);
+#define CATEKV_SW(RG) \
+  if (rg == RG) { hipLaunchKernelGGL((score_wave_kernel<RG, MODE, 0, 0>), grid, dim3(kSwThreads), 0, s, a); return hipGetLastError(); }
+  const int rg = sw_row_tiles(a.R);
+  CATEKV_SW(1) CATEKV_SW(2) CATEKV_SW(4) CATEKV_SW(8) CATEKV_SW(16)
+#undef CATEKV_SW
+  return hipErrorInvalidValue;
+}
+
+}  // namespace catekv
