@@ -93,6 +93,8 @@ struct SelectGeom {
   int n_colblk;            // column blocks of the score passes
   int64_t wcb_tokens;      // the same of the bf16 passes (score_wave.h); never more blocks than n_colblk
   int wn_colblk, unit_log;
+  int64_t fcb_tokens;      // the same of the fp32 passes; never fewer blocks than n_colblk
+  int fn_colblk;
   int heads[128];
 };
 
@@ -112,7 +114,7 @@ inline int score_waves(int dtype, int rows_pad) {
 // rows_pad query rows on a device of n_cu compute units; at most
 // kMaxBlockTokens (the kernels address a block's K rows with 32-bit offsets).
 constexpr int64_t kMaxBlockTokens = (int64_t)1 << 22;
-int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu);
+int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu, int min_tiles);
 // bf16 row counts whose two passes run on score_wave.h.  512 rows keep the
 // 16-wave workgroups of score.h: 31 + 30 us against 36 + 29 at 39939 keys of
 // 4 heads (one pass over both sums is score_wave.h's at any row count).
@@ -155,8 +157,8 @@ struct ScoreGeom {
   int64_t q_pos0;
   int causal;
   double k_pct, alpha;
-  int64_t cb_tokens, wcb_tokens;
-  int n_colblk, wn_colblk;
+  int64_t cb_tokens, wcb_tokens, fcb_tokens;
+  int n_colblk, wn_colblk, fn_colblk;
 };
 
 size_t score_workspace_bytes(const ScoreGeom& g);

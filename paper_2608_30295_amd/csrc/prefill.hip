@@ -824,15 +824,19 @@ static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Score workgroups run in a single round: as many as the device holds at once
 // (the bf16 residency: two workgroups per compute unit, whose LDS rings fill
 // 128 KB of its 160 KB, or one 16-wave workgroup at 512 rows; fp32 beyond 128
-// rows runs in two rounds), each over whole 64-column tiles, at least four
-// and at most kMaxBlockTokens columns (more rounds beyond).  The count
-// depends on the rows but not on the dtype, so workspace sizes do not either.
-int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu) {
+// rows runs in two rounds), each over whole 64-column tiles, at least
+// min_tiles of them and at most kMaxBlockTokens columns (more rounds beyond).
+// bf16 blocks hold at least four tiles.  An fp32 tile is one serial chain of
+// 128 to 512 MFMAs of a sixteenth of the bf16 rate, so there every tile of a
+// short row gets a workgroup: 4064 keys of 4 heads, 128 rows: 24.0 -> 11.5 us
+// per pass against four tiles each.  Workspaces are sized for the larger
+// count, so they do not depend on the dtype.
+int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu, int min_tiles) {
   const int64_t slots = (int64_t)std::max(1, n_cu) * (score_waves(CATEKV_BF16, rows_pad) > 8 ? 1 : 2);
   const int64_t per_head = std::max<int64_t>(1, slots / std::max(1, n_heads));
   int64_t cb = (std::max<int64_t>(n_keys, 1) + per_head - 1) / per_head;
   cb = (cb + kTileTok - 1) / kTileTok * kTileTok;
-  return std::min<int64_t>(std::max<int64_t>(cb, 4 * kTileTok), kMaxBlockTokens);
+  return std::min<int64_t>(std::max<int64_t>(cb, min_tiles * kTileTok), kMaxBlockTokens);
 }
 
 // One workgroup of score_wave.h per compute unit, in a single round; at least
@@ -853,7 +857,7 @@ static SelectLayout select_layout(const SelectGeom& g) {
   SelectLayout L{};
   const int rp = score_rows_pad(g.G * g.l_obs);
   size_t o = 0;
-  L.rowpart = o; o += align256((size_t)g.n_sel * g.n_colblk * rp * sizeof(float2));
+  L.rowpart = o; o += align256((size_t)g.n_sel * g.fn_colblk * rp * sizeof(float2));
   L.rowoff = o; o += align256((size_t)g.n_sel * rp * sizeof(float));
   // per-key column mass only when BlockMax cannot be fused into the score pass
   // (cs not dividing the 64-column tile)
@@ -937,8 +941,8 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
   a.key_off = 0; a.n_keys = g.n_keys;
   const OnePass op = bf ? one_pass(g, L) : OnePass{};
   const bool wave = bf && (op.n_cand > 0 || score_wave_rows(rp));
-  a.cb_tokens = wave ? g.wcb_tokens : g.cb_tokens;
-  a.n_colblk = wave ? g.wn_colblk : g.n_colblk;
+  a.cb_tokens = wave ? g.wcb_tokens : bf ? g.cb_tokens : g.fcb_tokens;
+  a.n_colblk = wave ? g.wn_colblk : bf ? g.n_colblk : g.fn_colblk;
   a.rp = rp; a.unit_log = g.unit_log;
   a.q_pos0 = g.n - g.l_obs; a.causal = 0; a.c = kLog2e / sqrtf((float)kD);
   for (int i = 0; i < g.n_sel; ++i) a.heads[i] = g.heads[i];
@@ -1058,6 +1062,10 @@ hipError_t launch_topk(const float* S, int n_rows, int64_t n, int b, int32_t* id
     s2.list = cand;
     s2.list_len = n_small * k_eff;
     launch_topk_fused<4>(s1, s2, (unsigned)n_small, n_rows, arrive, stream);
+  } else if (n <= kTopkThreads) {   // a lane's passes over its scores follow their number: 508 chunks 11.0 -> 4.6 us
+    hipLaunchKernelGGL((topk_wave_kernel<1>), dim3(n_rows), dim3(kTopkThreads), 0, stream, a);
+  } else if (n <= kTopkSmallSlice) {
+    hipLaunchKernelGGL((topk_wave_kernel<4>), dim3(n_rows), dim3(kTopkThreads), 0, stream, a);
   } else if (n <= kTopkSlice) {
     hipLaunchKernelGGL((topk_wave_kernel<16>), dim3(n_rows), dim3(kTopkThreads), 0, stream, a);
   } else if (n <= 2 * kTopkSlice) {
@@ -1106,10 +1114,11 @@ static ScoreLayout score_layout(const ScoreGeom& g) {
   ScoreLayout L{};
   const int rp = score_rows_pad(g.G * g.lq);
   size_t o = 0;
-  L.rowpart = o; o += align256((size_t)g.hkv * g.n_colblk * rp * sizeof(float2));
+  L.rowpart = o; o += align256((size_t)g.hkv * g.fn_colblk * rp * sizeof(float2));
   L.rowoff = o; o += align256((size_t)g.hkv * rp * sizeof(float));
   L.obs = o; o += align256((size_t)g.hkv * g.lq * g.n_keys * sizeof(float));
-  L.cv = o; o += align256(cv_workspace_bytes(g.hkv, g.lq, g.n_keys, g.n_colblk));
+  L.cv = o; o += align256(std::max(cv_workspace_bytes(g.hkv, g.lq, g.n_keys, g.n_colblk),
+                                    cv_workspace_bytes(g.hkv, g.lq, g.n_keys, g.fn_colblk)));
   L.total = o;
   return L;
 }
@@ -1124,15 +1133,18 @@ hipError_t launch_score(int dtype, const ScoreGeom& g, const void* q_rows, const
   const int rp = score_rows_pad(R);
   ScoreArgs a{};
   a.q = q_rows; a.k = k; a.hkv = g.hkv; a.lq = g.lq; a.G = g.G; a.R = R; a.n = g.n;
-  a.key_off = g.l_init; a.n_keys = g.n_keys; a.cb_tokens = g.cb_tokens; a.n_colblk = g.n_colblk;
+  const bool bf = dtype == CATEKV_BF16;
+  a.key_off = g.l_init; a.n_keys = g.n_keys;
+  a.cb_tokens = bf ? g.cb_tokens : g.fcb_tokens;
+  a.n_colblk = bf ? g.n_colblk : g.fn_colblk;
   a.rp = rp; a.unit_log = 5;
   a.q_pos0 = g.q_pos0; a.causal = g.causal; a.c = kLog2e / sqrtf((float)kD);
   for (int i = 0; i < g.hkv; ++i) a.heads[i] = i;
   a.rowpart = reinterpret_cast<float2*>(w + L.rowpart);
   a.rowoff = reinterpret_cast<const float*>(w + L.rowoff);
   a.obs = reinterpret_cast<float*>(w + L.obs);
-  a.cv = cv_link(w + L.cv, g.hkv, g.lq, g.n_keys, g.n_colblk, kCvMaxSub);
-  const dim3 grid(g.n_colblk, g.hkv);
+  a.cv = cv_link(w + L.cv, g.hkv, g.lq, g.n_keys, a.n_colblk, kCvMaxSub);
+  const dim3 grid(a.n_colblk, g.hkv);
   ScoreArgs r = a;          // row statistics: the blocks of the bf16 pass
   if (dtype == CATEKV_BF16 && score_wave_rows(rp)) {
     r.cb_tokens = g.wcb_tokens;
