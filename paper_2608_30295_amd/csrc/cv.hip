@@ -131,8 +131,9 @@ __device__ __forceinline__ double phi_of(double xlo, double xhi, int64_t N, doub
 // ---------------------------------------------------------------------------
 
 // The sample's first two radix digits give the 22-bit key prefixes holding
-// sample ranks lo s / N -+ (8 sigma + 32), sigma the binomial spread of a
-// sample rank; the bracket is every key with a prefix in that range.  As
+// sample ranks lo s / N -+ (5 sigma + 16), sigma the binomial spread of a
+// sample rank (a miss, which only costs the radix route, once in ~10^6 heads;
+// at the 0.996 percentile 0.95% of A is gathered, against 1.35% at 8 sigma + 32); the bracket is every key with a prefix in that range.  As
 // x_(lo) >= the bracket's bottom f_lo, Phi >= alpha f_lo: t_lo is that bound
 // less 2^-40 relative (far beyond the rounding of the fp64 interpolation),
 // rounded down to a float.
@@ -142,6 +143,10 @@ constexpr int kSamplePer = kCvSamples / kSampleThreads;
 __global__ __launch_bounds__(kSampleThreads) void cv_sample_kernel(const float* __restrict__ samples, int64_t N,
                                                                    double k_pct, double alpha, CvState* st,
                                                                    uint32_t* __restrict__ hist, int hkv) {
+  // first digit: most samples share a few dozen of the 2048 bins, so the lanes
+  // of a wave count into kCopies histograms
+  constexpr int kCopies = 8;
+  __shared__ uint32_t s_hc[kCopies][kBins + 4];
   __shared__ uint32_t s_h[kBins];
   __shared__ uint32_t s_h2[2][kBins];
   __shared__ int64_t s_tot[kSampleThreads / 64];
@@ -149,29 +154,37 @@ __global__ __launch_bounds__(kSampleThreads) void cv_sample_kernel(const float* 
   __shared__ int64_t s_pos[2];
   const int h = blockIdx.x;
   const int t = threadIdx.x;
+  const int64_t ns = cv_sample_count(N);
+  const float* sh = samples + (size_t)h * kCvSamples;
+  float v[kSamplePer];   // a thread's samples are kSampleThreads apart
+#pragma unroll
+  for (int u = 0; u < kSamplePer; ++u) v[u] = sh[std::min<int64_t>(u * kSampleThreads + t, ns - 1)];
   for (int p = 0; p < 4; ++p)
     for (int i = t; i < kBins; i += kSampleThreads) hist[((size_t)p * hkv + h) * kBins + i] = 0;
-  for (int i = t; i < kBins; i += kSampleThreads) s_h[i] = 0;
+  for (int i = t; i < kCopies * (kBins + 4); i += kSampleThreads) (&s_hc[0][0])[i] = 0;
   for (int i = t; i < 2 * kBins; i += kSampleThreads) s_h2[i / kBins][i % kBins] = 0;
   const int64_t rank = (int64_t)floor((double)(N - 1) * k_pct);
   __syncthreads();
-  const int64_t ns = cv_sample_count(N);
-  const float* sh = samples + (size_t)h * kCvSamples;
-  float v[kSamplePer];
 #pragma unroll
-  for (int u = 0; u < kSamplePer; ++u) v[u] = sh[std::min<int64_t>((int64_t)t * kSamplePer + u, ns - 1)];
+  for (int u = 0; u < kSamplePer; ++u)
+    if (u * kSampleThreads + t < ns) atomicAdd(&s_hc[t & (kCopies - 1)][ord_key(v[u]) >> 21], 1u);
+  __syncthreads();
+  for (int i = t; i < kBins; i += kSampleThreads) {
+    uint32_t c = 0;
 #pragma unroll
-  for (int u = 0; u < kSamplePer; ++u) hist_add(s_h, (int64_t)t * kSamplePer + u < ns, ord_key(v[u]) >> 21);
+    for (int k = 0; k < kCopies; ++k) c += s_hc[k][i];
+    s_h[i] = c;
+  }
   const double rs = (double)rank * (double)ns / (double)N;
   const double pq = (double)rank / (double)N;
-  const double m = 8.0 * sqrt((double)ns * pq * (1.0 - pq)) + 32.0;
+  const double m = 5.0 * sqrt((double)ns * pq * (1.0 - pq)) + 16.0;
   const int64_t lo_s = (int64_t)fmax(0.0, floor(rs - m)), hi_s = (int64_t)fmin((double)(ns - 1), ceil(rs + m));
   locate_ranks<kSampleThreads>(s_h, kBins, lo_s, hi_s, s_tot, s_bin, s_pos);
   const uint32_t bl = s_bin[0], bh = s_bin[1];
   const int64_t rl = s_pos[0], rh = s_pos[1];
 #pragma unroll
   for (int u = 0; u < kSamplePer; ++u) {
-    const bool ok = (int64_t)t * kSamplePer + u < ns;
+    const bool ok = u * kSampleThreads + t < ns;
     const uint32_t key = ord_key(v[u]);
     if (ok && (key >> 21) == bl) atomicAdd(&s_h2[0][(key >> 10) & 0x7FF], 1u);
     if (ok && (key >> 21) == bh) atomicAdd(&s_h2[1][(key >> 10) & 0x7FF], 1u);
@@ -256,31 +269,18 @@ __device__ __forceinline__ void flush_hist(const uint32_t* s_h, uint32_t* __rest
     if (s_h[i]) atomicAdd(&g[i], s_h[i]);
 }
 
-// nb (<= 64) consecutive pair buffers starting at buffer `first`, seen as
-// one index space: s_pre[w] = pairs before buffer w (filled by the first
-// wave, all fills loaded at once); returns the total.  Item k lies in the
-// last buffer w with s_pre[w] <= k.
-__device__ uint32_t buffer_prefix(const uint32_t* __restrict__ pfill, size_t first, int nb, uint32_t* s_pre) {
-  const int t = threadIdx.x;
-  if (t < 64) {
-    const uint32_t f = t < nb ? pfill[first + t] : 0u;
-    uint32_t x = f;
+// The pairs of one buffer, by one wave: 4 per lane and round, every load
+// issued (clamped), then used; f(valid, pair) on every lane.
+template <typename F>
+__device__ __forceinline__ void wave_pairs(const uint2* __restrict__ p, uint32_t fill, F&& f) {
+  const int lane = threadIdx.x & 63;
+  for (uint32_t i0 = 0; i0 < fill; i0 += 4 * 64) {
+    uint2 e[4];
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t y = __shfl_up(x, off);
-      if (t >= off) x += y;
-    }
-    if (t < nb) s_pre[t] = x - f;
-    if (t == nb - 1) s_pre[nb] = x;
+    for (int u = 0; u < 4; ++u) e[u] = p[min(i0 + u * 64 + lane, fill - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f(i0 + u * 64 + lane < fill, e[u]);
   }
-  __syncthreads();
-  return s_pre[nb];
-}
-__device__ __forceinline__ const uint2* buffer_item(const uint2* __restrict__ pairs, size_t first, int nb,
-                                                    uint32_t capw, const uint32_t* s_pre, uint32_t k) {
-  int w = 0;
-  while (w + 1 < nb && s_pre[w + 1] <= k) ++w;
-  return pairs + (first + w) * capw + (k - s_pre[w]);
 }
 
 // ---------------------------------------------------------------------------
@@ -293,8 +293,9 @@ __device__ __forceinline__ const uint2* buffer_item(const uint2* __restrict__ pa
 
 constexpr int kListCap = kCvListCap;
 constexpr int kRegions = 8;        // pair buffers per listing workgroup
-constexpr int kShortList = 1024;   // lists resolved by counting ranks
-constexpr int kListStage = 2048;   // entries staged before a reservation (a round adds <= 1024)
+constexpr int kShortList = 256;    // lists resolved by counting ranks (its cost grows with the square: 14 us at 1024)
+constexpr int kHeldList = 8;       // entries per thread of a longer list read once and held
+constexpr int kStage = 128;        // list entries a wave stages before it reserves their places
 
 // Offsets key - k_lo of one workgroup's gathered pairs, 4 per thread and
 // round (the same trip count on every lane); f(inside the bracket, offset).
@@ -371,7 +372,14 @@ __device__ double resolve_phi(CvState& S, const uint32_t* __restrict__ hist0, co
       eq = s_x[2];
       next = min(s_x[3], min2);
     } else {
-      const bool from_list = nl <= (uint32_t)kListCap;
+      const bool from_list = nl <= (uint32_t)kListCap, held = nl <= kHeldList * 256u;
+      uint32_t e[kHeldList];
+#pragma unroll
+      for (int u = 0; u < kHeldList; ++u) {
+        const uint32_t i = u * 256 + t;
+        e[u] = held ? __hip_atomic_load(&lh[min(i, nl - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kNone;
+        if (i >= nl) e[u] = kNone;
+      }
       int bits = sh1;
       while (bits > 0) {
         const int d = bits > 11 ? 11 : bits;
@@ -388,7 +396,10 @@ __device__ double resolve_phi(CvState& S, const uint32_t* __restrict__ hist0, co
           hist_add(s_h, ok && hi == P, (o >> nsh) & dmask);
           if (last && ok && hi > P) mn = min(mn, o);
         };
-        if (from_list) {
+        if (held) {
+#pragma unroll
+          for (int u = 0; u < kHeldList; ++u) visit(e[u] != kNone, e[u]);
+        } else if (from_list) {
           for (uint32_t k0 = 0; k0 < nl; k0 += 4 * 256) {
             uint32_t o[4];
 #pragma unroll
@@ -436,12 +447,8 @@ __global__ __launch_bounds__(256) void cv_list_kernel(const float* __restrict__ 
   __shared__ int64_t s_tot[4];
   __shared__ uint32_t s_bin[3];
   __shared__ int64_t s_pos[2];
-  __shared__ uint32_t s_min;
-  __shared__ uint32_t s_stage[kListStage];
-  __shared__ uint32_t s_nl, s_lbase;
-  __shared__ uint32_t s_x[4];
+  __shared__ uint32_t s_x[4], s_n[4], s_base;
   __shared__ int s_last;
-  __shared__ uint32_t s_pre[kRegions + 1];
   const int h = blockIdx.y;
   const int t = threadIdx.x, lane = t & 63;
   CvState& S = st[h];
@@ -465,57 +472,53 @@ __global__ __launch_bounds__(256) void cv_list_kernel(const float* __restrict__ 
   const int64_t rem1 = s_pos[0];
   uint32_t* lh = list + (size_t)h * kListCap;
   if (sh1 > 0) {
-    if (t == 0) {
-      s_nl = 0;
-      s_min = kNone;
-    }
-    __syncthreads();
-    uint32_t mn = kNone;
-    auto out = [&]() {             // the staged entries to the list, one reservation
-      const uint32_t nst = s_nl;
-      if (nst) {
-        if (t == 0) s_lbase = atomicAdd(&S.n_list, nst);
-        __syncthreads();
-        // atomic writes: each entry is at the coherence point when it returns
-        for (uint32_t i = t; i < nst; i += 256)
-          if (s_lbase + i < (uint32_t)kListCap) atomicExch(&lh[s_lbase + i], s_stage[i]);
-      }
-      __syncthreads();
-      if (t == 0) s_nl = 0;
-      __syncthreads();
+    // Each wave walks buffers of its own and stages the entries of the bin
+    // in its own part of LDS until it reserves their places in the list with
+    // one atomic (a reservation per hit serialises on the head's counter) and
+    // writes them atomically (an entry is at the coherence point when its
+    // write returns).  One workgroup-wide stage behind a barrier per 1024
+    // pairs, with a search for each pair's buffer, took 22 us at 8 heads of
+    // 64 x 131008 scores and 86 us at 32 x 1048416; this takes 18.9 and 29.9.
+    const int r0 = blockIdx.x * kRegions, r1 = min(cb, r0 + kRegions), wave = t >> 6;
+    uint32_t* stage = &s_h[wave * kStage];    // (s_h is free until the head is resolved)
+    static_assert(4 * kStage <= kBins, "four waves' stages");
+    uint32_t mn = kNone, staged = 0;          // staged: wave-uniform, at most 64 between two pairs
+    auto flush = [&]() {
+      uint32_t base = 0;
+      if (lane == 0) base = atomicAdd(&S.n_list, staged);
+      base = __shfl(base, 0);
+      for (uint32_t i = lane; i < staged; i += 64)
+        if (base + i < (uint32_t)kListCap) atomicExch(&lh[base + i], stage[i]);
+      staged = 0;
     };
-    const int r0 = blockIdx.x * kRegions, nb = min(cb, r0 + kRegions) - r0;
-    const size_t first = (size_t)h * cb + r0;
-    const uint32_t total = buffer_prefix(pfill, first, nb, s_pre);
-    for (uint32_t i0 = 0; i0 < total; i0 += 4 * 256) {   // the same trip count on every lane
-      uint32_t o[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {   // every load issued (clamped), then used
-        const uint32_t i = i0 + u * 256 + t;
-        const uint32_t x = buffer_item(pairs, first, nb, capw, s_pre, min(i, total - 1))->x;
-        o[u] = i < total ? (x | 0x80000000u) - k_lo : kNone;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const bool ok = o[u] <= span;
-        const bool in = ok && (o[u] >> sh1) == b1;
-        if (ok && (o[u] >> sh1) > b1) mn = min(mn, o[u]);
+    for (int r = r0 + wave; r < r1; r += 4) {
+      const size_t buf = (size_t)h * cb + r;
+      wave_pairs(pairs + buf * capw, pfill[buf], [&](bool ok, uint2 e) {
+        const uint32_t o = (e.x | 0x80000000u) - k_lo;
+        ok = ok && o <= span;
+        if (ok && (o >> sh1) > b1) mn = min(mn, o);
+        const bool in = ok && (o >> sh1) == b1;
         const uint64_t bal = __builtin_amdgcn_ballot_w64(in);
         if (bal) {
-          uint32_t base = 0;
-          if (lane == 0) base = atomicAdd(&s_nl, (uint32_t)__builtin_popcountll(bal));
-          base = __shfl(base, 0) + mbcnt(bal);
-          if (in) s_stage[base] = o[u];
+          if (in) stage[staged + mbcnt(bal)] = o;
+          staged += (uint32_t)__builtin_popcountll(bal);
+          if (staged > kStage - 64) flush();
         }
-      }
-      __syncthreads();
-      if (s_nl > (uint32_t)(kListStage - 4 * 256)) out();   // room for the next round
+      });
     }
-    out();
-    for (int off = 32; off > 0; off >>= 1) mn = min(mn, (uint32_t)__shfl_xor((int)mn, off));
-    if (lane == 0 && mn != kNone) atomicMin(&s_min, mn);
+    // what is left of the four stages goes out together
+    if (lane == 0) s_n[wave] = staged;
     __syncthreads();
-    if (t == 0 && s_min != kNone) atomicMin(&S.min2, s_min);
+    const uint32_t n0 = s_n[0], n1 = s_n[1], n2 = s_n[2], n3 = s_n[3];
+    if (n0 + n1 + n2 + n3) {
+      if (t == 0) s_base = atomicAdd(&S.n_list, n0 + n1 + n2 + n3);
+      __syncthreads();
+      const uint32_t base = s_base + (wave > 0 ? n0 : 0) + (wave > 1 ? n1 : 0) + (wave > 2 ? n2 : 0);
+      for (uint32_t i = lane; i < staged; i += 64)
+        if (base + i < (uint32_t)kListCap) atomicExch(&lh[base + i], stage[i]);
+    }
+    for (int off = 32; off > 0; off >>= 1) mn = min(mn, (uint32_t)__shfl_xor((int)mn, off));
+    if (lane == 0 && mn != kNone) atomicMin(&S.min2, mn);
   }
   // arrival once this workgroup's list entries, minimum and count have all
   // completed (device-scope atomics, waited for); the last one takes Phi
@@ -535,7 +538,7 @@ __global__ __launch_bounds__(256) void cv_list_kernel(const float* __restrict__ 
 //    C_j^2.  Radix route: the second key digit over A.
 // ---------------------------------------------------------------------------
 
-constexpr int kColWin = 8192;      // columns counted in LDS at a time
+constexpr int kColWin = 16384;     // columns counted in LDS at a time (16-bit counters: at most lq <= 512 each)
 
 __global__ __launch_bounds__(256) void cv_columns_kernel(const float* __restrict__ A, int64_t N, CvState* st,
                                                          const uint32_t* __restrict__ hist1,
@@ -543,8 +546,7 @@ __global__ __launch_bounds__(256) void cv_columns_kernel(const float* __restrict
                                                          const uint32_t* __restrict__ pfill, uint32_t capw, int nsub,
                                                          int n_colblk, int64_t cb_tokens,
                                                          int64_t n_keys) {
-  __shared__ uint32_t s_e[kColWin];
-  __shared__ uint32_t s_pre[kCvMaxSub + 1];
+  __shared__ uint32_t s_e[kColWin / 2];
   __shared__ int64_t s_tot[4];
   __shared__ uint32_t s_bin[3];
   __shared__ int64_t s_pos[2];
@@ -577,30 +579,23 @@ __global__ __launch_bounds__(256) void cv_columns_kernel(const float* __restrict
   const int b = blockIdx.x;
   const int64_t c0 = (int64_t)b * cb_tokens, c1 = c0 + cb_tokens < n_keys ? c0 + cb_tokens : n_keys;
   const size_t first = ((size_t)h * n_colblk + b) * nsub;
-  const uint32_t total = buffer_prefix(pfill, first, nsub, s_pre);
   unsigned long long a1 = 0, a2 = 0;
   for (int64_t w0 = c0; w0 < c1; w0 += kColWin) {
-    const int nw = (int)std::min<int64_t>(kColWin, c1 - w0);
+    const int nw = (int)(c1 - w0 < kColWin ? c1 - w0 : kColWin);
     __syncthreads();
-    for (int i = t; i < nw; i += 256) s_e[i] = 0;
+    for (int i = t; i < (nw + 1) / 2; i += 256) s_e[i] = 0;
     __syncthreads();
-    for (uint32_t i0 = 0; i0 < total; i0 += 4 * 256) {
-      uint2 e[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)   // every load issued (clamped), then used
-        e[u] = *buffer_item(pairs, first, nsub, capw, s_pre, min(i0 + u * 256 + t, total - 1));
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float x = __uint_as_float(e[u].x);
-        const int64_t rel = (int64_t)e[u].y - w0;
-        if (i0 + u * 256 + t < total && rel >= 0 && rel < nw && (double)x >= phi) atomicAdd(&s_e[rel], 1u);
-      }
-    }
+    for (int w = t >> 6; w < nsub; w += 4)    // each wave walks buffers of its own
+      wave_pairs(pairs + (first + w) * capw, pfill[first + w], [&](bool ok, uint2 e) {
+        const int64_t rel = (int64_t)e.y - w0;
+        if (ok && rel >= 0 && rel < nw && (double)__uint_as_float(e.x) >= phi)
+          atomicAdd(&s_e[rel >> 1], rel & 1 ? 0x10000u : 1u);
+      });
     __syncthreads();
-    for (int l = t; l < nw; l += 256) {
-      const unsigned long long c = s_e[l];
-      a1 += c;
-      a2 += c * c;
+    for (int l = t; l < (nw + 1) / 2; l += 256) {
+      const unsigned long long x = s_e[l] & 0xFFFFu, y = s_e[l] >> 16;
+      a1 += x + y;
+      a2 += x * x + y * y;
     }
   }
   const unsigned long long t1 = block_sum256(a1, s_red);
@@ -760,7 +755,8 @@ CvLink cv_link(void* ws, int hkv, int lq, int64_t n_keys, int n_colblk, int nsub
   c.list = reinterpret_cast<uint32_t*>(w + L.list);
   c.pairs = reinterpret_cast<uint2*>(w + L.pairs);
   c.pfill = reinterpret_cast<uint32_t*>(w + L.pfill);
-  c.capw = pair_cap((int64_t)lq * n_keys, (int64_t)n_colblk * kCvMaxSub);
+  // the region of kCvMaxSub buffers per block, split among the pass's waves
+  c.capw = pair_cap((int64_t)lq * n_keys, (int64_t)n_colblk * kCvMaxSub) * (uint32_t)kCvMaxSub / (uint32_t)nsub & ~3u;
   c.nsub = nsub;
   return c;
 }

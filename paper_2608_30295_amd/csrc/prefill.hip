@@ -43,7 +43,12 @@ __device__ float2 rowstats_exact(const ScoreArgs& a, int sel, int row, int b, in
   return make_float2(m, sum16(l));
 }
 
-constexpr int kMergeRows = 16;    // rows per 256-thread workgroup of the merge
+constexpr int kMergeRows = 16;    // rows per workgroup of the merge (its first 256 threads)
+// Threads per workgroup: 256 for a selection; 1024 for CV, whose workgroup
+// also takes 512 to 2048 sampled entries, one 256-byte K row each: a thread's
+// second and fourth entry wait behind its first (8 heads, 64 rows x 131008
+// keys: 16.4 -> 10.4 us; 32 x 1048416: 28.7 -> 20.5 us).
+constexpr int kMergeThreads = 256, kMergeThreadsCv = 1024;
 
 // CV (observation matrix): the sampled entries of A whose query rows are
 // the workgroup's kMergeRows rows (G divides kMergeRows, so a query's G rows
@@ -51,7 +56,7 @@ constexpr int kMergeRows = 16;    // rows per 256-thread workgroup of the merge
 // products, one entry per thread at a time with the rows' Q in LDS; the
 // sample only has to place the quantile, the bracketing pass classifies A's
 // values as the observation pass computes them.
-template <typename T, int G>
+template <typename T, int G, int NT>
 __device__ void cv_sample_rows(const ScoreArgs& a, int sel, int row0, float my_off) {
   __shared__ float s_q[kMergeRows][kD + 1];   // +1: rows start in different banks
   __shared__ float s_o[kMergeRows];
@@ -59,7 +64,7 @@ __device__ void cv_sample_rows(const ScoreArgs& a, int sel, int row0, float my_o
   const int t = threadIdx.x;
   const uint32_t n_keys = (uint32_t)a.n_keys;
   const int64_t N = (int64_t)a.lq * a.n_keys;     // below 2^32 (the entry points check)
-  for (int e = t; e < kMergeRows * kD; e += 256) {
+  for (int e = t; e < kMergeRows * kD; e += NT) {
     const int rr = e / kD, d = e % kD, r = row0 + rr;
     const int i = r / G, g = r - (r / G) * G;
     const T* q = reinterpret_cast<const T*>(a.q) + ((size_t)(h * G + g) * a.lq + (r < a.R ? i : 0)) * kD;
@@ -68,7 +73,7 @@ __device__ void cv_sample_rows(const ScoreArgs& a, int sel, int row0, float my_o
     else x = q[d];
     s_q[rr][d] = r < a.R ? x : 0.f;
   }
-  if ((t & 15) == 0) s_o[t >> 4] = my_off;
+  if ((t & 15) == 0 && t < 16 * kMergeRows) s_o[t >> 4] = my_off;
   __syncthreads();
   const int q0 = row0 / G, q1 = min(a.lq, (row0 + kMergeRows) / G);   // this workgroup's queries
   if (q0 >= q1) return;
@@ -83,7 +88,7 @@ __device__ void cv_sample_rows(const ScoreArgs& a, int sel, int row0, float my_o
   const int64_t s1 = s1r < ns ? s1r : ns;
   const T* kh = reinterpret_cast<const T*>(a.k) + (size_t)h * a.n * kD;
   const float invG = 1.0f / (float)G;
-  for (int64_t s = s0 + t; s < s1; s += 256) {
+  for (int64_t s = s0 + t; s < s1; s += NT) {
     const uint32_t ent = (uint32_t)(all ? s : (s / kCvSampleRun) * stride + (s % kCvSampleRun));
     const uint32_t i = ent / n_keys, j = ent - (ent / n_keys) * n_keys;
     if ((int)i < q0 || (int)i >= q1) continue;
@@ -138,21 +143,22 @@ __device__ void cv_sample_rows(const ScoreArgs& a, int sel, int row0, float my_o
 // for rows with no visible key and for padding rows.  16 lanes share a row
 // and walk its column blocks with independent loads, then reduce over DPP.
 // A block whose sum overflowed is recomputed exactly first.
-template <typename T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) void rowstats_merge_kernel(ScoreArgs a, int rpad,
-                                                                                               float* __restrict__ off) {
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 4))) void rowstats_merge_kernel(ScoreArgs a, int rpad,
+                                                                                              float* __restrict__ off) {
   const int sel = blockIdx.y;
   const int n_colblk = a.n_colblk, R = a.R;
   if (blockIdx.x == 0 && blockIdx.y == 0)
     for (int i = threadIdx.x; i < a.n_zero; i += blockDim.x) a.zero_u32[i] = 0;
   const int row = blockIdx.x * kMergeRows + (threadIdx.x >> 4);
   const int ln = threadIdx.x & 15;
-  const bool ok = row < R;
+  const bool mine = NT == 256 || threadIdx.x < 256;   // wave-uniform
+  const bool ok = mine && row < R;
   const float2* p = a.rowpart + (size_t)sel * n_colblk * rpad + (ok ? row : 0);
   float M = kMInit, L = 0.f;
   bool bad = false;
   constexpr int UNR = 8;
-  for (int b0 = ln; b0 < n_colblk; b0 += 16 * UNR) {
+  for (int b0 = ln; mine && b0 < n_colblk; b0 += 16 * UNR) {
     float2 v[UNR];
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
@@ -188,8 +194,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
   const float M16 = max16(M);
   L = sum16(L * fast_exp2(M - M16));
   const float o = (ok && L > 0.f) ? M16 + __log2f(L) : INFINITY;
-  if (ln == 0 && row < rpad) off[(size_t)sel * rpad + row] = o;
-  if (a.rho) {   // one-pass selection: every block's offset is the row's estimate
+  if (mine && ln == 0 && row < rpad) off[(size_t)sel * rpad + row] = o;
+  if (NT == kMergeThreads && a.rho) {   // one-pass selection: every block's offset is the row's estimate
     const float r = ok && L > 0.f ? fast_exp2(p[0].x - o) : 0.f;
     const bool redo = ok && (bad || !(r < INFINITY));
     const float rw = max_xor32(max_xor16(r));
@@ -199,12 +205,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 4))) voi
       atomicMax(&a.rho[sel], __float_as_uint(rw));
     }
   }
-  if (a.cv.samples) {
+  if (NT == kMergeThreadsCv) {
     const int r0 = blockIdx.x * kMergeRows;
-    if (a.G == 1) cv_sample_rows<T, 1>(a, sel, r0, o);
-    else if (a.G == 2) cv_sample_rows<T, 2>(a, sel, r0, o);
-    else if (a.G == 4) cv_sample_rows<T, 4>(a, sel, r0, o);
-    else cv_sample_rows<T, 8>(a, sel, r0, o);
+    if (a.G == 1) cv_sample_rows<T, 1, NT>(a, sel, r0, o);
+    else if (a.G == 2) cv_sample_rows<T, 2, NT>(a, sel, r0, o);
+    else if (a.G == 4) cv_sample_rows<T, 4, NT>(a, sel, r0, o);
+    else cv_sample_rows<T, 8, NT>(a, sel, r0, o);
   }
 }
 
@@ -973,7 +979,7 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
     m.rowoff = est;
     e = launch_score_both(grid, stream, m);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(rowstats_merge_kernel<uint16_t>, mgrid, dim3(256), 0, stream, a, rp, off);
+    hipLaunchKernelGGL((rowstats_merge_kernel<uint16_t, kMergeThreads>), mgrid, dim3(kMergeThreads), 0, stream, a, rp, off);
     if (!a.cs_fused)
       hipLaunchKernelGGL(chunk_max_kernel, cgrid, dim3(256), 0, stream, a.colmass, g.n_keys, g.cs, g.n_chunks, S,
                          (const uint32_t*)nullptr);
@@ -1008,8 +1014,8 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
   } else {
     e = launch_score_rowstats(dtype, g.G, false, rp, grid, stream, a);
     if (e != hipSuccess) return e;
-    if (dtype == CATEKV_BF16) hipLaunchKernelGGL(rowstats_merge_kernel<uint16_t>, mgrid, dim3(256), 0, stream, a, rp, off);
-    else hipLaunchKernelGGL(rowstats_merge_kernel<float>, mgrid, dim3(256), 0, stream, a, rp, off);
+    if (dtype == CATEKV_BF16) hipLaunchKernelGGL((rowstats_merge_kernel<uint16_t, kMergeThreads>), mgrid, dim3(kMergeThreads), 0, stream, a, rp, off);
+    else hipLaunchKernelGGL((rowstats_merge_kernel<float, kMergeThreads>), mgrid, dim3(kMergeThreads), 0, stream, a, rp, off);
   }
   e = launch_score_colmass(dtype, rp, grid, stream, a);
   if (e != hipSuccess) return e;
@@ -1125,6 +1131,12 @@ static ScoreLayout score_layout(const ScoreGeom& g) {
 
 size_t score_workspace_bytes(const ScoreGeom& g) { return score_layout(g).total; }
 
+// waves per workgroup of the observation passes (launch_score_mt; one query
+// per row keeps eight at 512 rows)
+static int obs_waves(int dtype, int G, int rows_pad) {
+  return G == 1 ? std::min(score_waves(dtype, rows_pad), 8) : score_waves(dtype, rows_pad);
+}
+
 hipError_t launch_score(int dtype, const ScoreGeom& g, const void* q_rows, const void* k,
                         float* cv_out, void* ws, hipStream_t stream) {
   const ScoreLayout L = score_layout(g);
@@ -1143,20 +1155,22 @@ hipError_t launch_score(int dtype, const ScoreGeom& g, const void* q_rows, const
   a.rowpart = reinterpret_cast<float2*>(w + L.rowpart);
   a.rowoff = reinterpret_cast<const float*>(w + L.rowoff);
   a.obs = reinterpret_cast<float*>(w + L.obs);
-  a.cv = cv_link(w + L.cv, g.hkv, g.lq, g.n_keys, a.n_colblk, kCvMaxSub);
-  const dim3 grid(a.n_colblk, g.hkv);
+  a.cv = cv_link(w + L.cv, g.hkv, g.lq, g.n_keys, a.n_colblk, obs_waves(dtype, g.G, rp));
   ScoreArgs r = a;          // row statistics: the blocks of the bf16 pass
-  if (dtype == CATEKV_BF16 && score_wave_rows(rp)) {
+  if (bf && score_wave_rows(rp)) {
     r.cb_tokens = g.wcb_tokens;
     r.n_colblk = g.wn_colblk;
   }
+  const dim3 grid(a.n_colblk, g.hkv);
   hipError_t e = launch_score_rowstats(dtype, g.G, g.causal, rp, dim3(r.n_colblk, g.hkv), stream, r);
   if (e != hipSuccess) return e;
   if (dtype == CATEKV_BF16)
-    hipLaunchKernelGGL(rowstats_merge_kernel<uint16_t>, dim3((rp + kMergeRows - 1) / kMergeRows, g.hkv), dim3(256), 0,
+    hipLaunchKernelGGL((rowstats_merge_kernel<uint16_t, kMergeThreadsCv>), dim3((rp + kMergeRows - 1) / kMergeRows, g.hkv),
+                       dim3(kMergeThreadsCv), 0,
                        stream, r, rp, reinterpret_cast<float*>(w + L.rowoff));
   else
-    hipLaunchKernelGGL(rowstats_merge_kernel<float>, dim3((rp + kMergeRows - 1) / kMergeRows, g.hkv), dim3(256), 0,
+    hipLaunchKernelGGL((rowstats_merge_kernel<float, kMergeThreadsCv>), dim3((rp + kMergeRows - 1) / kMergeRows, g.hkv),
+                       dim3(kMergeThreadsCv), 0,
                        stream, r, rp, reinterpret_cast<float*>(w + L.rowoff));
   // the merge also took the sampled entries of A; the bracket from them,
   // the bracketing pass, A itself only for the heads the bracket missed

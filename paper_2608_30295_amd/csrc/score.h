@@ -499,8 +499,6 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a) {
       a.cv.pfill[((size_t)sel * a.n_colblk + cb) * a.cv.nsub + wave] = min(wfill, a.cv.capw);
       if (wfill > a.cv.capw) atomicOr(&a.cv.st[sel].phi_over, 1u);
     }
-    if (threadIdx.x >= W && threadIdx.x < a.cv.nsub)   // buffers of waves this shape does not have
-      a.cv.pfill[((size_t)sel * a.n_colblk + cb) * a.cv.nsub + threadIdx.x] = 0;
     // Each wave reads its own pairs back (its stores have completed: the
     // wait above): the bracket entries are counted and histogrammed by
     // their first digit (key - k_lo) >> shift1, and the pairs at or above
