@@ -23,6 +23,7 @@ constexpr int kDppXor1 = 0xB1;
 constexpr int kDppXor2 = 0x4E;
 constexpr int kDppHalfMirror = 0x141;
 constexpr int kDppMirror = 0x140;
+constexpr int kDppRor8 = 0x128;      // row_ror:8 = lane ^ 8 within a row of 16
 
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {

@@ -163,14 +163,27 @@ __global__ __launch_bounds__(WAVES * 64) void decode_stream_kernel(DecodeArgs a)
   __shared__ float s_o[WAVES][G][kD];
   __shared__ float s_m[WAVES][G], s_l[WAVES][G];
 
-  const int seg_lo = a.worker_seg[blockIdx.x], seg_hi = a.worker_seg[blockIdx.x + 1];
+  // A one-workgroup-per-CU plan lists the worker's segments with their count
+  // and slots in one place: two dependent loads before the first rows are
+  // requested (the list, then the view) instead of three.
+  const bool v2 = a.variant == kDecodeStreamV2;
+  const V2Item* list = a.v2items + (size_t)blockIdx.x * kDecodeV2MaxSeg;
+  const int seg_lo = v2 ? 0 : a.worker_seg[blockIdx.x];
+  const int seg_hi = v2 ? (int)((uint32_t)list[0].bh_n >> 24) : a.worker_seg[blockIdx.x + 1];
   for (int sg = seg_lo; sg < seg_hi; ++sg) {
-    const DecodeItem it = a.items[sg];
+    struct { int32_t bh, t0, t1, slot; } it;      // slot < 0: the segment covers its view
+    if (v2) {
+      const V2Item e = list[sg];
+      it = {e.bh_n & 0xFFFFFF, e.t0, e.t1, e.slot};
+    } else {
+      const DecodeItem e = a.items[sg];
+      const ViewInfo vi = a.views[e.bh];
+      it = {e.bh, e.t0, e.t1, vi.n_parts == 1 ? -1 : vi.first_slot + e.part};
+    }
     const int bh = it.bh;
     const int b = bh / hkv, h = bh - b * hkv;
     const catekv_kv_ptrs view = a.kv[bh];
     int64_t len = a.lens[bh];
-    const ViewInfo vi = a.views[bh];
     len = len < 0 ? 0 : len;
     const int t0 = it.t0;
     const int t_end = (int)((int64_t)it.t1 < len ? (int64_t)it.t1 : len);
@@ -254,27 +267,21 @@ __global__ __launch_bounds__(WAVES * 64) void decode_stream_kernel(DecodeArgs a)
     }
 
     // ---- merge the 8 token groups of the wave (lanes l, l^8, l^16, l^32) ----
+    // row rotation and row swaps on the vector unit: the 72 values of G = 4
+    // through the LDS crossbar were 216 exchanges in the way of every segment
+    auto sum_groups = [](float x) {
+      x += dpp<kDppRor8>(x);
+      return add_xor32(add_xor16(x));
+    };
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      float M = m[g];
-      M = fmaxf(M, shfl_xor(M, 8));
-      M = fmaxf(M, shfl_xor(M, 16));
-      M = fmaxf(M, shfl_xor(M, 32));
+      float M = fmaxf(m[g], dpp<kDppRor8>(m[g]));
+      M = max_xor32(max_xor16(M));
       const float corr = m[g] == -INFINITY ? 0.f : fast_exp2((m[g] - M) * c);
-      float lg = l[g] * corr;
-      lg += shfl_xor(lg, 8);
-      lg += shfl_xor(lg, 16);
-      lg += shfl_xor(lg, 32);
-      l[g] = lg;
+      l[g] = sum_groups(l[g] * corr);
       m[g] = M;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        float x = o[g][e] * corr;
-        x += shfl_xor(x, 8);
-        x += shfl_xor(x, 16);
-        x += shfl_xor(x, 32);
-        o[g][e] = x;
-      }
+      for (int e = 0; e < 16; ++e) o[g][e] = sum_groups(o[g][e] * corr);
     }
 
     // ---- merge the waves through LDS ---------------------------------------
@@ -293,7 +300,7 @@ __global__ __launch_bounds__(WAVES * 64) void decode_stream_kernel(DecodeArgs a)
     __syncthreads();
 
     const size_t row0 = (size_t)b * hq + (size_t)h * G;
-    float* slot = a.slots + (size_t)(vi.first_slot + it.part) * SF;
+    float* slot = a.slots + (size_t)it.slot * SF;
     for (int t = threadIdx.x; t < G * kD; t += NT) {
       const int g = t / kD, e = t - g * kD;
       float M = -INFINITY;
@@ -307,7 +314,7 @@ __global__ __launch_bounds__(WAVES * 64) void decode_stream_kernel(DecodeArgs a)
         Ov += s_o[w][g][e] * cw;
       }
       const float Mn = M * scale;               // natural-log units of the scaled score
-      if (vi.n_parts == 1) emit(a.out, a.lse, row0 + g, e, Mn, L, Ov);
+      if (it.slot < 0) emit(a.out, a.lse, row0 + g, e, Mn, L, Ov);
       else put_slot<G>(slot, g, e, Mn, L, Ov);
     }
   }

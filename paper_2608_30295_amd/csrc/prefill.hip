@@ -1057,7 +1057,7 @@ hipError_t launch_topk(const float* S, int n_rows, int64_t n, int b, int32_t* id
   // and a second launch picks among their k best.  Measured: k = 256 of 16384
   // gains ~1.7 us on three rows, k = 1024 loses ~2.7 us, so k is held to at
   // most an eighth of a slice.
-  const bool few_short_rows = ws && n > kTopkSmallSlice && n <= 2 * kTopkSlice &&
+  const bool few_short_rows = ws && n > 2 * kTopkSmallSlice && n <= 2 * kTopkSlice &&
                               8 * k_eff <= kTopkSmallSlice && (int64_t)n_rows * n_small <= 2048;
   uint32_t* arrive = reinterpret_cast<uint32_t*>(ws);
   TopkCand* cand = ws ? reinterpret_cast<TopkCand*>(reinterpret_cast<char*>(ws) + topk_counter_bytes(n_rows)) : nullptr;
@@ -1072,6 +1072,8 @@ hipError_t launch_topk(const float* S, int n_rows, int64_t n, int b, int32_t* id
     hipLaunchKernelGGL((topk_wave_kernel<1>), dim3(n_rows), dim3(kTopkThreads), 0, stream, a);
   } else if (n <= kTopkSmallSlice) {
     hipLaunchKernelGGL((topk_wave_kernel<4>), dim3(n_rows), dim3(kTopkThreads), 0, stream, a);
+  } else if (n <= 2 * kTopkSmallSlice) {
+    hipLaunchKernelGGL((topk_wave_kernel<8>), dim3(n_rows), dim3(kTopkThreads), 0, stream, a);
   } else if (n <= kTopkSlice) {
     hipLaunchKernelGGL((topk_wave_kernel<16>), dim3(n_rows), dim3(kTopkThreads), 0, stream, a);
   } else if (n <= 2 * kTopkSlice) {
