@@ -143,16 +143,12 @@ __device__ void cv_sample_rows(const ScoreArgs& a, int sel, int row0, float my_o
 // for rows with no visible key and for padding rows.  16 lanes share a row
 // and walk its column blocks with independent loads, then reduce over DPP.
 // A block whose sum overflowed is recomputed exactly first.
-template <typename T, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 4))) void rowstats_merge_kernel(ScoreArgs a, int rpad,
-                                                                                              float* __restrict__ off) {
-  const int sel = blockIdx.y;
+// Called by whole waves, four rows each; `mine` is wave-uniform.
+template <typename T>
+__device__ __forceinline__ float merge_row(const ScoreArgs& a, int rpad, float* __restrict__ off, int sel, int row, bool mine,
+                                           bool with_rho) {
   const int n_colblk = a.n_colblk, R = a.R;
-  if (blockIdx.x == 0 && blockIdx.y == 0)
-    for (int i = threadIdx.x; i < a.n_zero; i += blockDim.x) a.zero_u32[i] = 0;
-  const int row = blockIdx.x * kMergeRows + (threadIdx.x >> 4);
   const int ln = threadIdx.x & 15;
-  const bool mine = NT == 256 || threadIdx.x < 256;   // wave-uniform
   const bool ok = mine && row < R;
   const float2* p = a.rowpart + (size_t)sel * n_colblk * rpad + (ok ? row : 0);
   float M = kMInit, L = 0.f;
@@ -195,7 +191,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 4))) void
   L = sum16(L * fast_exp2(M - M16));
   const float o = (ok && L > 0.f) ? M16 + __log2f(L) : INFINITY;
   if (mine && ln == 0 && row < rpad) off[(size_t)sel * rpad + row] = o;
-  if (NT == kMergeThreads && a.rho) {   // one-pass selection: every block's offset is the row's estimate
+  if (with_rho) {   // one-pass selection: every block's offset is the row's estimate
     const float r = ok && L > 0.f ? fast_exp2(p[0].x - o) : 0.f;
     const bool redo = ok && (bad || !(r < INFINITY));
     const float rw = max_xor32(max_xor16(r));
@@ -205,6 +201,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 4))) void
       atomicMax(&a.rho[sel], __float_as_uint(rw));
     }
   }
+  return o;
+}
+
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 4))) void rowstats_merge_kernel(ScoreArgs a, int rpad,
+                                                                                              float* __restrict__ off) {
+  const int sel = blockIdx.y;
+  if (blockIdx.x == 0 && blockIdx.y == 0)
+    for (int i = threadIdx.x; i < a.n_zero; i += blockDim.x) a.zero_u32[i] = 0;
+  const bool mine = NT == kMergeThreads || threadIdx.x < kMergeThreads;
+  const float o = merge_row<T>(a, rpad, off, sel, blockIdx.x * kMergeRows + (threadIdx.x >> 4), mine,
+                               NT == kMergeThreads && a.rho);
   if (NT == kMergeThreadsCv) {
     const int r0 = blockIdx.x * kMergeRows;
     if (a.G == 1) cv_sample_rows<T, 1, NT>(a, sel, r0, o);
@@ -736,6 +744,22 @@ __global__ __launch_bounds__(256) void row_estimate_kernel(ScoreArgs a, float* _
   }
 }
 
+// The row-statistics merge and, in workgroups of their own, the candidates'
+// top-k: neither needs the other, and side by side they take the top-k's time
+// (6.5 + 12.8 -> 13.6 us at 5 heads, 256 rows, 16376 chunks).
+template <int PER>
+__global__ __launch_bounds__(kTopkThreads) __attribute__((amdgpu_waves_per_eu(1, 4)))
+void merge_topk_kernel(ScoreArgs a, int rpad, float* __restrict__ off, TopkArgs t, int n_sel) {
+  if ((int)blockIdx.x < n_sel) {
+    topk_body<PER, kTopkRow>(t, blockIdx.x, 0, 1);
+    return;
+  }
+  const int blk = blockIdx.x - n_sel, per_head = rpad / (kTopkThreads / 16);
+  if (blk == 0)
+    for (int i = threadIdx.x; i < a.n_zero; i += kTopkThreads) a.zero_u32[i] = 0;
+  merge_row<uint16_t>(a, rpad, off, blk / per_head, blk % per_head * (kTopkThreads / 16) + (threadIdx.x >> 4), true, true);
+}
+
 // The b best of each head's candidates by exact score, and whether they are
 // the head's b best (redo[sel] is set if that is not shown).  Grid: one
 // workgroup per head.  Both masses are sums of positive terms rounded to
@@ -979,12 +1003,22 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
     m.rowoff = est;
     e = launch_score_both(grid, stream, m);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((rowstats_merge_kernel<uint16_t, kMergeThreads>), mgrid, dim3(kMergeThreads), 0, stream, a, rp, off);
     if (!a.cs_fused)
       hipLaunchKernelGGL(chunk_max_kernel, cgrid, dim3(256), 0, stream, a.colmass, g.n_keys, g.cs, g.n_chunks, S,
                          (const uint32_t*)nullptr);
-    e = launch_topk(S, g.n_sel, g.n_chunks, op.n_cand, cand, w + L.topk, stream);
-    if (e != hipSuccess) return e;
+    if (g.n_chunks <= 2 * kTopkSlice) {   // rows that one workgroup selects from
+      TopkArgs t{};
+      t.S = S; t.n = g.n_chunks; t.k = t.b = op.n_cand; t.out = cand;
+      const dim3 mt(g.n_sel + g.n_sel * (rp / (kTopkThreads / 16)));
+      if (g.n_chunks <= kTopkSlice)
+        hipLaunchKernelGGL((merge_topk_kernel<16>), mt, dim3(kTopkThreads), 0, stream, a, rp, off, t, g.n_sel);
+      else
+        hipLaunchKernelGGL((merge_topk_kernel<32>), mt, dim3(kTopkThreads), 0, stream, a, rp, off, t, g.n_sel);
+    } else {
+      hipLaunchKernelGGL((rowstats_merge_kernel<uint16_t, kMergeThreads>), mgrid, dim3(kMergeThreads), 0, stream, a, rp, off);
+      e = launch_topk(S, g.n_sel, g.n_chunks, op.n_cand, cand, w + L.topk, stream);
+      if (e != hipSuccess) return e;
+    }
     ScoreArgs ga = a;       // the candidates' columns, 32 per wave
     ga.cand = cand;
     ga.cand_cs = g.cs;
