@@ -115,9 +115,10 @@ inline int score_waves(int dtype, int rows_pad) {
 // kMaxBlockTokens (the kernels address a block's K rows with 32-bit offsets).
 constexpr int64_t kMaxBlockTokens = (int64_t)1 << 22;
 int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu, int min_tiles);
-// bf16 row counts whose two passes run on score_wave.h.  512 rows keep the
-// 16-wave workgroups of score.h: 31 + 30 us against 36 + 29 at 39939 keys of
-// 4 heads (one pass over both sums is score_wave.h's at any row count).
+// bf16 row counts whose passes run on score_wave.h.  512 rows keep the 16-wave
+// workgroups of score.h, whose query rows stay in registers: 31 + 30 us
+// against 36 + 29 at 39939 keys of 4 heads (there the offsets and sums would
+// not fit the registers, and the query rows take 139 KB of LDS).
 inline bool score_wave_rows(int rows_pad) { return rows_pad < 512; }
 // score_block_tokens for the bf16 passes of score_wave.h, whose waves take units of
 // 1 << unit_log keys.

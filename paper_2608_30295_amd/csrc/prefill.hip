@@ -945,7 +945,7 @@ constexpr int64_t kOnePassScores = (int64_t)128 << 20;
 static OnePass one_pass(const SelectGeom& g, const SelectLayout& L) {
   OnePass p{};
   const int rp = score_rows_pad(g.G * g.l_obs);
-  if (kOnePassShare * g.b > g.n_chunks || (int64_t)g.n_sel * rp * g.n_keys < kOnePassScores) return p;
+  if (!score_wave_rows(rp) || kOnePassShare * g.b > g.n_chunks || (int64_t)g.n_sel * rp * g.n_keys < kOnePassScores) return p;
   const int64_t nc = 2 * (int64_t)g.b + g.b / 2 + 64;
   const int64_t n_slices = (g.n_chunks + kTopkSlice - 1) / kTopkSlice;
   if (nc >= g.n_chunks || nc > 8 * kTopkThreads || (g.n_chunks > 2 * kTopkSlice && n_slices * nc > 2 * kTopkSlice)) return p;
@@ -970,7 +970,7 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
   const bool bf = dtype == CATEKV_BF16;
   a.key_off = 0; a.n_keys = g.n_keys;
   const OnePass op = bf ? one_pass(g, L) : OnePass{};
-  const bool wave = bf && (op.n_cand > 0 || score_wave_rows(rp));
+  const bool wave = bf && score_wave_rows(rp);
   a.cb_tokens = wave ? g.wcb_tokens : bf ? g.cb_tokens : g.fcb_tokens;
   a.n_colblk = wave ? g.wn_colblk : bf ? g.n_colblk : g.fn_colblk;
   a.rp = rp; a.unit_log = g.unit_log;

@@ -114,7 +114,6 @@ struct ScoreArgs {
   // score_wave.h
   int rp;                 // rows per block of rowpart and per head of rowoff (R padded)
   int g_log;              // log2(G)
-  int lb_log;             // log2 of the consecutive queries per group head in the LDS row order
   int unit_log;           // log2 of the keys per unit of a wave's run (5, or 6 where chunks span 64 keys)
   // one-pass selection (prefill.hip)
   const uint32_t* gate;   // kColMass: heads with a zero word are left alone

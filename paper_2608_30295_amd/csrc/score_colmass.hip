@@ -8,7 +8,7 @@ namespace catekv {
 
 hipError_t launch_score_colmass(int dtype, int rows_pad, dim3 grid, hipStream_t s, const ScoreArgs& a) {
   if (dtype == CATEKV_BF16) {
-    if (score_wave_rows(rows_pad) || a.gate) return launch_score_wave<kColMass>(grid, s, a);
+    if (score_wave_rows(rows_pad)) return launch_score_wave<kColMass>(grid, s, a);
     hipLaunchKernelGGL((score_kernel<uint16_t, 16, 2, kColMass, 0, false, 4>), grid, dim3(1024), 0, s, a);
     return hipGetLastError();
   }

@@ -8,9 +8,6 @@ namespace catekv {
 hipError_t launch_score_rowstats(int dtype, int G, bool causal, int rows_pad, dim3 grid, hipStream_t s,
                                  const ScoreArgs& a) {
   if (dtype == CATEKV_BF16) {
-    // 512 rows: the 16-wave workgroup, whose query rows stay in registers, is
-    // the faster one (39939 keys, 4 heads: 31 us against 36; see
-    // score_wave_rows)
     if (score_wave_rows(rows_pad)) return launch_score_wave<kRowStats>(grid, s, a);
 #define CATEKV_SC(GG, CC) \
   if ((GG == 0 || G == GG) && causal == CC) { \

@@ -31,18 +31,11 @@ constexpr int kSwWaves = 8;                 // waves per workgroup, one workgrou
 constexpr int kSwThreads = kSwWaves * 64;
 constexpr int kSwRow = 17;                  // 16-byte units per LDS query row (16 + 1: rows start in different banks)
 
-// Query rows lie in LDS by slot: lb = 1 << lb_log consecutive queries of one
-// group head, then the next group head, then the next lb queries.  With lb =
-// 32 a 32-row tile holds one group head's rows, so the G rows of a query sit
-// in the same lane of G tiles and the group mean needs no exchange.  With lb
-// = 16 (at most 16 queries, G >= 2) a tile holds two group heads.
-struct SwSlot {
+// Row r of the score block is query i = r / G of group head g = r % G.
+struct SwRow {
   int i, g;
 };
-__device__ __forceinline__ SwSlot sw_slot(int s, int lb_log, int g_log) {
-  const int t = s >> lb_log;
-  return {(t >> g_log << lb_log) | (s & ((1 << lb_log) - 1)), t & ((1 << g_log) - 1)};
-}
+__device__ __forceinline__ SwRow sw_row(int r, int g_log) { return {r >> g_log, r & ((1 << g_log) - 1)}; }
 
 // kBoth: a row's sum is estimated from kSwEstGroups samples; the third
 // smallest estimate is taken (any finite number is a valid weight: sums that
@@ -65,24 +58,21 @@ __device__ __forceinline__ float sw_est_pick(const float* e8) {
 // key of accumulator register r within its 32-key tile
 __device__ __forceinline__ constexpr int sw_key(int r) { return (r & 3) + 8 * (r >> 2); }
 
-// RG 32-row tiles.  GO, LB: group size and queries per tile (observation
-// modes only, which add the G rows of a query).
-template <int RG, int MODE, int GO, int LB>
+// RG 32-row tiles
+template <int RG, int MODE>
 __global__ __launch_bounds__(kSwThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void score_wave_kernel(ScoreArgs a) {
   constexpr int KS = 8;                     // 16-dim steps of the contraction
   __shared__ uint4 s_q[RG * 32 * kSwRow];
-  // Row offsets (log2 units) and sums of exp2(s c - offset): registers up to
-  // 256 rows, LDS for 512 (kRowStats: each wave's own; the offset is a bf16
-  // number, which any number near the row's maximum may be, so that all of it
-  // fits the 160 KB).
+  // Row offsets (log2 units) and sums of exp2(s c - offset) lie in registers,
+  // the row tiles unrolled; kBoth has none left for them: LDS, and the row
+  // tiles are a loop (unrolled, the compiler spills).
   constexpr bool RS = MODE == kRowStats, BOTH = MODE == kBoth, SUMS = RS || BOTH, GATHER = MODE == kColGather;
-  constexpr bool REG = RG <= 8 && !BOTH;    // offsets in registers
-  constexpr bool REGL = RG <= 8 && !BOTH;   // sums in registers
-  __shared__ uint16_t s_off16[RS ? kSwWaves : 1][RS ? RG * 32 : 1];
-  __shared__ float s_off[RS || REG ? 1 : RG * 32];   // (the same for all waves)
+  static_assert(RG <= 8, "at most 256 rows");
+  __shared__ float s_woff[RS ? kSwWaves : 1][RS ? RG * 32 : 1];   // kRowStats: each wave's own offsets, at the end
+  __shared__ float s_off[BOTH ? RG * 32 : 1];
   __shared__ float s_l[SUMS ? kSwWaves : 1][SUMS ? RG * 32 : 1];
-  float off_r[REG ? RG : 1], l_r[REGL ? RG : 1];
+  float off_r[BOTH ? 1 : RG], l_r[BOTH ? 1 : RG];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, half = lane >> 5;
   const int sel = blockIdx.y, cb = blockIdx.x;
@@ -119,7 +109,7 @@ void score_wave_kernel(ScoreArgs a) {
   const uint32_t voff = (uint32_t)n * (kD * 2) + (uint32_t)half * 16;
   uint4 kf[2][2][KS];
   // shares a tile is requested in (kBoth: two row tiles each, looped over)
-  constexpr int kSlots = BOTH ? (RG < 2 ? 1 : RG / 2) : RG < 8 ? RG : 8;
+  constexpr int kSlots = BOTH ? (RG < 2 ? 1 : RG / 2) : RG;
   // share `slot` of the 32 keys from column col, and of those `step` further (NF = 2), all valid, into f:
   // at least four 32-byte steps together, so that a request's 128-byte lines are used whole
   auto load_slot = [&](uint4 (&f)[2][KS], int col, auto nf_tag, int slot, int step = 32) {
@@ -152,33 +142,30 @@ void score_wave_kernel(ScoreArgs a) {
 #pragma unroll
   for (int u = 0; u < QP; ++u) {
     const int e = u * kSwThreads + threadIdx.x;
-    const SwSlot q = sw_slot(e >> 4, a.lb_log, a.g_log);
+    const SwRow q = sw_row(e >> 4, a.g_log);
     const uint32_t row = (uint32_t)(h * G + q.g) * a.lq + min(q.i, a.lq - 1);
     qv[u] = ldg16(reinterpret_cast<const char*>(a.q) + (size_t)row * (kD * 2) + (e & 15) * 16);
   }
   auto load_off = [&](int s) -> float {
-    const SwSlot q = sw_slot(s, a.lb_log, a.g_log);
+    const SwRow q = sw_row(s, a.g_log);
     if (q.i >= a.lq) return INFINITY;
     const float* o = a.rowoff + ((size_t)sel * a.rp + q.i * G + q.g) * (BOTH ? kSwEstGroups : 1);
     return BOTH ? sw_est_pick(o) : *o;
   };
-#pragma unroll
-  for (int rg = 0; rg < (REG ? RG : 0); ++rg) off_r[rg] = RS ? kMInit : load_off(rg * 32 + n);
-#pragma unroll
-  for (int rg = 0; rg < (REGL ? RG : 0); ++rg) l_r[rg] = 0.f;
-  if constexpr (SUMS && !REGL) {
-    for (int s = lane; s < RG * 32; s += 64) {
-      if (RS) s_off16[wave][s] = (uint16_t)(__builtin_bit_cast(uint32_t, kMInit) >> 16);
-      s_l[wave][s] = 0.f;
-    }
-  }
-  if (!RS && !REG) {
+  if constexpr (BOTH) {
+    for (int s = lane; s < RG * 32; s += 64) s_l[wave][s] = 0.f;
     for (int s = threadIdx.x; s < RG * 32; s += kSwThreads) s_off[s] = load_off(s);
+  } else {
+#pragma unroll
+    for (int rg = 0; rg < RG; ++rg) {
+      off_r[rg] = RS ? kMInit : load_off(rg * 32 + n);
+      l_r[rg] = 0.f;
+    }
   }
 #pragma unroll
   for (int u = 0; u < QP; ++u) {
     const int e = u * kSwThreads + threadIdx.x;
-    const bool ok = sw_slot(e >> 4, a.lb_log, a.g_log).i < a.lq;
+    const bool ok = sw_row(e >> 4, a.g_log).i < a.lq;
     s_q[(e >> 4) * kSwRow + (e & 15)] = ok ? qv[u] : make_uint4(0, 0, 0, 0);
   }
   barrier_lds_only();
@@ -189,7 +176,7 @@ void score_wave_kernel(ScoreArgs a) {
   if (pu > 0) load_all(kf[1], c_lo, T1{});
 
   const uint4* qn = s_q + n * kSwRow + half;
-  float cm[2][16];        // kColMass: column sums of the tile; observation modes: the group's sums
+  float cm[2][16];        // column modes: the lane's column sums of the tile
   const float c = a.c;
 
   auto mfma = [&](const uint4 (&f)[KS], const uint4 (&bf)[KS]) {
@@ -267,11 +254,10 @@ void score_wave_kernel(ScoreArgs a) {
     constexpr bool MASK = decltype(mask_tag)::value, FIRST = decltype(first_tag)::value;
     auto rows = [&](int rg) {
       float off;
-      if constexpr (REG) off = off_r[rg];
-      else if constexpr (RS) off = __uint_as_float((uint32_t)s_off16[wave][rg * 32 + n] << 16);
-      else off = s_off[rg * 32 + n];
+      if constexpr (BOTH) off = s_off[rg * 32 + n];
+      else off = off_r[rg];
       int last = c_hi - 1 - col - 4 * half;               // MASK: last visible key of this lane's row in the tile
-      if (MASK) last = min(last, lim + sw_slot(rg * 32 + n, a.lb_log, a.g_log).i - col - 4 * half);
+      if (MASK) last = min(last, lim + sw_row(rg * 32 + n, a.g_log).i - col - 4 * half);
       float ls = 0.f;
 #pragma unroll
       for (int t = 0; t < NT2; ++t) {
@@ -283,24 +269,19 @@ void score_wave_kernel(ScoreArgs a) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[r] = t * 32 + sw_key(r) <= last ? acc[r] : -INFINITY;
         }
-        if (FIRST && t == 0) {
+        if constexpr (FIRST) if (t == 0) {
           float m = acc[0];
 #pragma unroll
           for (int r = 1; r < 16; ++r) m = fmaxf(m, acc[r]);
-          // c > 0: the maximum of s c is c times that of s
-          off = __uint_as_float(__float_as_uint(fmaxf(kMInit, max_xor32(m) * c)) & 0xffff0000u);
-          if constexpr (REG) {
-            off_r[rg] = off;
-          } else {
-            s_off16[wave][rg * 32 + n] = (uint16_t)(__float_as_uint(off) >> 16);   // both halves write the same
-          }
+          off = fmaxf(kMInit, max_xor32(m) * c);          // c > 0: the maximum of s c is c times that of s
+          off_r[rg] = off;
         }
         float p[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(acc[r], c, -off));
         if (!RS) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) cm[t][r] = REG && rg == 0 ? p[r] : cm[t][r] + p[r];
+          for (int r = 0; r < 16; ++r) cm[t][r] = !BOTH && rg == 0 ? p[r] : cm[t][r] + p[r];
         }
         if (SUMS) {
 #pragma unroll
@@ -311,14 +292,14 @@ void score_wave_kernel(ScoreArgs a) {
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      if constexpr (SUMS && REGL) {
+      if constexpr (RS) {
         l_r[rg] += ls;
-      } else if constexpr (SUMS) {
+      } else if constexpr (BOTH) {
         ls = add_xor32(ls);                               // both halves hold the same row
         if (half == 0) atomicAdd(&s_l[wave][rg * 32 + n], ls);   // this wave's own word
       }
     };
-    if (!RS && !REG) {
+    if (BOTH) {
 #pragma unroll
       for (int t = 0; t < NT2; ++t)
 #pragma unroll
@@ -327,7 +308,7 @@ void score_wave_kernel(ScoreArgs a) {
 #pragma unroll
     for (int slot = 0; slot < kSlots; ++slot) {
       ahead(slot);
-      if constexpr (REGL) {
+      if constexpr (!BOTH) {
         rows(slot);
       } else {
 #pragma unroll 1
@@ -397,24 +378,26 @@ void score_wave_kernel(ScoreArgs a) {
 
   // ---- row sums: the lanes of a row, then the waves --------------------------
   if constexpr (SUMS) {
+    if constexpr (RS) {
 #pragma unroll
-    for (int rg = 0; rg < (REGL ? RG : 0); ++rg) {
-      const float ls = add_xor32(l_r[rg]);                // both halves hold the same row and offset
-      if (half == 0) {
-        if constexpr (RS) s_off16[wave][rg * 32 + n] = (uint16_t)(__float_as_uint(off_r[rg]) >> 16);
-        s_l[wave][rg * 32 + n] = ls;
+      for (int rg = 0; rg < RG; ++rg) {
+        const float ls = add_xor32(l_r[rg]);              // both halves hold the same row and offset
+        if (half == 0) {
+          s_woff[wave][rg * 32 + n] = off_r[rg];
+          s_l[wave][rg * 32 + n] = ls;
+        }
       }
     }
     __syncthreads();
     for (int s = threadIdx.x; s < RG * 32; s += kSwThreads) {
-      const SwSlot q = sw_slot(s, a.lb_log, a.g_log);
+      const SwRow q = sw_row(s, a.g_log);
       if (q.i >= a.lq) continue;
       float M = kMInit, L = 0.f;
       if constexpr (RS) {
         float2 v[kSwWaves];
 #pragma unroll
         for (int w = 0; w < kSwWaves; ++w) {
-          v[w] = make_float2(__uint_as_float((uint32_t)s_off16[w][s] << 16), s_l[w][s]);
+          v[w] = make_float2(s_woff[w][s], s_l[w][s]);
           M = fmaxf(M, v[w].x);
         }
 #pragma unroll
@@ -429,23 +412,21 @@ void score_wave_kernel(ScoreArgs a) {
   }
 }
 
-// 32-row tiles (1, 2, 4, 8 or 16) for `rows` slots
+// 32-row tiles (1, 2, 4 or 8) for up to 256 rows
 inline int sw_row_tiles(int rows) {
   int rg = 1;
   while (rg * 32 < rows) rg *= 2;
   return rg;
 }
 
-// row statistics and column mass: rows in their natural order (lb = 1)
 template <int MODE>
 inline hipError_t launch_score_wave(dim3 grid, hipStream_t s, ScoreArgs a) {
-  a.lb_log = 0;
   if (MODE == kRowStats) a.unit_log = 5;
   a.g_log = __builtin_ctz((unsigned)a.G);
 #define CATEKV_SW(RG) \
-  if (rg == RG) { hipLaunchKernelGGL((score_wave_kernel<RG, MODE, 0, 0>), grid, dim3(kSwThreads), 0, s, a); return hipGetLastError(); }
+  if (rg == RG) { hipLaunchKernelGGL((score_wave_kernel<RG, MODE>), grid, dim3(kSwThreads), 0, s, a); return hipGetLastError(); }
   const int rg = sw_row_tiles(a.R);
-  CATEKV_SW(1) CATEKV_SW(2) CATEKV_SW(4) CATEKV_SW(8) CATEKV_SW(16)
+  CATEKV_SW(1) CATEKV_SW(2) CATEKV_SW(4) CATEKV_SW(8)
 #undef CATEKV_SW
   return hipErrorInvalidValue;
 }
