@@ -673,7 +673,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_fused_kernel(TopkArgs s1, T
 // One-pass selection (bf16, long rows of keys, small budgets).  The column
 // mass needs every row's sum first, which took a pass of its own over K
 // (q.k again, K from HBM again).  Here the pass that sums the rows also adds
-// up the columns, with each row weighted by an estimate of its sum from 2048
+// up the columns, with each row weighted by an estimate of its sum from 1024
 // sampled keys instead of the sum itself: C'_j = sum_i rho_i^-1 w_i e_ij for
 // the true weights w_i, where rho_i = estimate / sum is known afterwards.  So
 // C_j <= max(rho) C'_j, and the chunks that can be among the b best are those
@@ -939,7 +939,11 @@ struct OnePass {
 };
 // Candidates per chunk of the budget: on Gaussian keys with 1% heavy hitters
 // the bound leaves 1.1 to 1.9 chunks per chunk kept, as long as the budget
-// keeps at most a 48th of the chunks; flatter scores need many more.
+// keeps at most a 48th of the chunks.  Flat scores (Gaussian keys without
+// heavy hitters) need 12 to 20, as the sample's noise spreads rho by 12%: such
+// heads are redone, 158 us against 140 for 131008 keys of 5 heads (two passes
+// each), where peaked ones take 102 against 121.  8192 sampled keys would
+// settle them in theory (1.5 to 3.3) but cost 8-12 us a call and left some.
 constexpr int64_t kOnePassShare = 48;
 constexpr int64_t kOnePassScores = (int64_t)128 << 20;
 static OnePass one_pass(const SelectGeom& g, const SelectLayout& L) {
