@@ -136,7 +136,7 @@ hipError_t launch_compact(int dtype, const void* k, const void* v, int hkv, int6
 
 // Indices of the min(b, n) largest of each row of S [n_rows][n] (ties to the
 // lower index), ascending, -1 padded to b.  ws: topk_workspace_bytes() bytes
-// (rows longer than 4096 scores are reduced slice by slice through it); its
+// (rows longer than 8192 scores may be reduced slice by slice through it); its
 // first n_rows 32-bit words must be zero on entry (an earlier launch of the
 // same call clears them) and are left zero.  gate: rows with a zero word are
 // left alone.

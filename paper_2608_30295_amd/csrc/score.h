@@ -7,8 +7,10 @@
 //   pass 2  p = exp2(s * log2(e) / sqrt(d) - offset), then either the column
 //           mass C_j = (1/G) sum_rows p (selection) or the group-mean
 //           observation matrix A[i][j] (CV).
-// Workgroup = 4 waves sharing one 64-token K tile staged in LDS; wave w owns
-// rows [w * MT * 16, (w + 1) * MT * 16) with their Q fragments in registers.
+// Workgroup = 4 to 16 waves sharing one 64-token K tile staged in LDS; wave w
+// owns rows [w * MT * 16, (w + 1) * MT * 16) with their Q fragments in
+// registers.  fp32, 512 rows and the observation passes run here; bf16 row
+// statistics and column mass up to 256 rows in score_wave.h.
 // Each pass is instantiated in a source file of its own (score_*.hip).
 #pragma once
 
