@@ -763,7 +763,9 @@ void merge_topk_kernel(ScoreArgs a, int rpad, float* __restrict__ off, TopkArgs 
 // The b best of each head's candidates by exact score, and whether they are
 // the head's b best (redo[sel] is set if that is not shown).  Grid: one
 // workgroup per head.  Both masses are sums of positive terms rounded to
-// fp32, within far less than the 1e-4 allowed for.
+// fp32, within far less than the 1e-4 allowed for.  A ratio below fp32's
+// normal numbers has been flushed to 0: the largest counts as the smallest
+// normal number at least.
 template <int PER>
 __global__ __launch_bounds__(kTopkThreads) void select_final_kernel(TopkArgs t, TopkCand* __restrict__ list,
                                                                     const int32_t* __restrict__ cand,
@@ -792,7 +794,8 @@ __global__ __launch_bounds__(kTopkThreads) void select_final_kernel(TopkArgs t, 
 #pragma unroll
     for (int w = 1; w < kTopkThreads / 64; ++w) lowest = fminf(lowest, s_min[w]);
     const float kth = __uint_as_float((tau & 0x80000000u) ? (tau & 0x7FFFFFFFu) : ~tau);
-    if (!(__uint_as_float(rho[sel]) * lowest * 1.0001f < kth)) redo[sel] = 1;
+    const float most = fmaxf(__uint_as_float(rho[sel]), 0x1p-126f);
+    if (!(most * lowest * 1.0001f < kth)) redo[sel] = 1;
   }
 }
 

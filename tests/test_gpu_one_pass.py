@@ -61,3 +61,64 @@ def test_one_pass_selection(kind, hq, hkv, l_obs, keys, cs, b):
             sc = np.full_like(sc, sc[0])
             assert np.array_equal(idx[heads.index(h)], np.arange(b))
         check_topk(idx[heads.index(h)], sc, b)
+
+
+# Scores at the ends of fp32's exponent range.  Keys lie on a few axes: with
+# queries 32 e_a + 0.25 e_b a key x e_a + y e_b scores 32 x + 0.25 y exactly,
+# x and y on bf16's grid.
+C = math.log2(math.e) / math.sqrt(128)      # log2 units per unit of q . k
+SAMPLES = 32                                 # 32-key tiles that the row sums are estimated from
+
+
+def _axes(log2, sx):
+    """x, y with 32 x + 0.25 y as close to log2 / C as y's grid allows; x of log2's sign, on a grid of sx."""
+    s = log2 / C
+    x = math.trunc(s / 32 / sx) * sx
+    y = torch.tensor((s - 32 * x) / 0.25).bfloat16().item()
+    return x, y
+
+
+def _random_heads(hkv, rows, n, head):
+    g = torch.Generator(device=DEV).manual_seed(n + head)
+    q = torch.randn((hkv, rows, 128), generator=g, device=DEV).bfloat16()
+    k = torch.empty((hkv, n, 128), dtype=torch.bfloat16, device=DEV)
+    for h in range(hkv):
+        x = torch.randn((n, 128), generator=g, device=DEV)
+        x[torch.rand(n, generator=g, device=DEV) < 0.01] *= 3
+        k[h] = x
+    q[head], k[head] = 0, 0
+    return q, k
+
+
+def _select_head(q, k, head, cs, b):
+    hkv = k.shape[0]
+    idx = ck.select_critical(q, k, list(range(hkv)), cs, b).cpu().numpy()
+    qf, kf = (t[head:head + 1].float().cpu().numpy().astype(np.float64) for t in (q, k))
+    sc = O.chunk_scores(qf, kf, 0, 1, q.shape[1], cs, 1 / math.sqrt(128))
+    return idx[head], sc
+
+
+def test_estimates_far_below_the_sums():
+    """Every row's sum lies 2^126 to 2^128 above its estimate, the spikes all
+    outside the sampled tiles: the rows' estimate-to-sum ratios are below
+    fp32's normal numbers, and the bound on the other chunks with them.  The
+    best chunk is one of row 0's; 70 chunks of row 1, whose ratio is three
+    times smaller, rank above it by their weighted mass."""
+    n_keys, head = 262144, 3
+    q, k = _random_heads(8, 2, n_keys + 2, head)
+    q[head, 0, 0], q[head, 0, 1], q[head, 1, 2], q[head, 1, 3] = 32, 0.25, 32, 0.25
+    base = math.log2(n_keys)                 # every other key scores 0
+    first = torch.arange(SAMPLES) * (n_keys - 32) // (SAMPLES - 1)
+    free = [c for c in range(100, n_keys // 8 - 8, 211) if ((first + 32 <= 8 * c) | (first >= 8 * c + 8)).all()]
+    best, a, b = free[75], free[:69], free[76:146]
+
+    def put(chunks, dim, log2):
+        x, y = _axes(log2, 0.25)
+        for c in chunks:
+            k[head, 8 * c + 5, dim], k[head, 8 * c + 5, dim + 1] = x, y
+    put([best], 0, base + 126.4 + math.log2(0.0165))
+    put(a, 0, base + 126.4 + math.log2((1 - 0.0165) / 69))
+    put(b, 2, base + 127.8 - math.log2(70))
+    idx, sc = _select_head(q, k, head, 8, 1)
+    assert np.argmax(sc) == best
+    check_topk(idx, sc, 1)
