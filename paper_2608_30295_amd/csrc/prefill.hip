@@ -765,13 +765,15 @@ void merge_topk_kernel(ScoreArgs a, int rpad, float* __restrict__ off, TopkArgs 
 // workgroup per head.  Both masses are sums of positive terms rounded to
 // fp32, within far less than the 1e-4 allowed for.  A ratio below fp32's
 // normal numbers has been flushed to 0: the largest counts as the smallest
-// normal number at least.
+// normal number at least.  So has a row's term of a weighted mass: each of
+// the rows may have lost as much there (rho > 1: its exact term need not be
+// that small), and once more in the mean over the group.
 template <int PER>
 __global__ __launch_bounds__(kTopkThreads) void select_final_kernel(TopkArgs t, TopkCand* __restrict__ list,
                                                                     const int32_t* __restrict__ cand,
                                                                     const float* __restrict__ mass, int cs, int64_t n_keys,
                                                                     const float* __restrict__ S, int64_t n_chunks,
-                                                                    const uint32_t* __restrict__ rho, uint32_t* redo) {
+                                                                    const uint32_t* __restrict__ rho, int rows, uint32_t* redo) {
   __shared__ float s_min[kTopkThreads / 64];
   const int sel = blockIdx.x, nc = (int)t.list_len;
   TopkCand* ls = list + (size_t)sel * nc;
@@ -795,7 +797,7 @@ __global__ __launch_bounds__(kTopkThreads) void select_final_kernel(TopkArgs t, 
     for (int w = 1; w < kTopkThreads / 64; ++w) lowest = fminf(lowest, s_min[w]);
     const float kth = __uint_as_float((tau & 0x80000000u) ? (tau & 0x7FFFFFFFu) : ~tau);
     const float most = fmaxf(__uint_as_float(rho[sel]), 0x1p-126f);
-    if (!(most * lowest * 1.0001f < kth)) redo[sel] = 1;
+    if (!(most * (lowest + (float)(rows + 1) * 0x1p-126f) * 1.0001f < kth)) redo[sel] = 1;
   }
 }
 
@@ -1045,7 +1047,7 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
     t.out = idx_out;
 #define CATEKV_FIN(PER) \
   hipLaunchKernelGGL((select_final_kernel<PER>), dim3(g.n_sel), dim3(kTopkThreads), 0, stream, t, list, cand, mass, g.cs, \
-                     g.n_keys, S, g.n_chunks, a.rho, redo)
+                     g.n_keys, S, g.n_chunks, a.rho, R, redo)
     if (op.n_cand <= 1 * kTopkThreads) CATEKV_FIN(1);
     else if (op.n_cand <= 2 * kTopkThreads) CATEKV_FIN(2);
     else if (op.n_cand <= 4 * kTopkThreads) CATEKV_FIN(4);

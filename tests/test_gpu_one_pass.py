@@ -122,3 +122,22 @@ def test_estimates_far_below_the_sums():
     idx, sc = _select_head(q, k, head, 8, 1)
     assert np.argmax(sc) == best
     check_topk(idx, sc, 1)
+
+
+def test_estimates_far_above_the_sums():
+    """Six keys carry the row's whole sum, one in each of six sampled groups:
+    the estimate is 341 times the sum, and against it every other key's
+    weight is below fp32's normal numbers, though its share of the exact mass
+    is not."""
+    n_keys, head = 262144, 3
+    q, k = _random_heads(8, 1, n_keys + 1, head)
+    q[head, 0, 0], q[head, 0, 1] = 32, 0.25
+    low, mid = _axes(-118.0, 0.25), _axes(-116.5, 0.25)
+    k[head, :n_keys, 0], k[head, :n_keys, 1] = low
+    upper = [20000 + 7 * i for i in range(200)]          # chunks with one key of 2^1.5 times the mass of the others
+    for c in upper:
+        k[head, 8 * c + 2, 0], k[head, 8 * c + 2, 1] = mid
+    for t in range(6):
+        k[head, (n_keys - 32) * t // (SAMPLES - 1) + 5, :2] = 0
+    idx, sc = _select_head(q, k, head, 8, 64)
+    check_topk(idx, sc, 64)
