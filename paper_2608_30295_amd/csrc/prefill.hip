@@ -173,12 +173,19 @@ __device__ __forceinline__ float merge_row(const ScoreArgs& a, int rpad, float* 
     for (int u = 0; u < UNR; ++u) L += v[u].y * fast_exp2(v[u].x - mb);
     M = mb;
   }
+  // One-pass selection: every block's sum is taken against the row's estimate,
+  // which is at most n_keys / 128 times the sum (2^24: n_keys < 2^31) where it
+  // is one.  A sum further below has no estimate behind it (the sampled scores
+  // were all -inf) and may have vanished: its blocks are all recomputed.
+  const float rsum = sum16(L);
+  const bool lost = with_rho && ok && !(rsum >= 0x1p-30f);
+  if (lost) M = kMInit, L = 0.f;
   // any overflowed block of this row: the 16 lanes recompute each of them
   // together, and lane 0 merges the exact statistics
-  const uint64_t any = __ballot(bad);
+  const uint64_t any = __ballot(bad || lost);
   if ((any >> (threadIdx.x & 48)) & 0xffffull) {
     for (int b = 0; b < n_colblk; ++b) {
-      if (p[(size_t)b * rpad].y <= 0x1.fffffep127f) continue;   // the same for the row's 16 lanes
+      if (!lost && p[(size_t)b * rpad].y <= 0x1.fffffep127f) continue;   // the same for the row's 16 lanes
       const float2 e = rowstats_exact<T>(a, sel, row, b, ln);
       if (ln == 0 && e.y > 0.f) {
         const float mb = fmaxf(M, e.x);
@@ -193,7 +200,7 @@ __device__ __forceinline__ float merge_row(const ScoreArgs& a, int rpad, float* 
   if (mine && ln == 0 && row < rpad) off[(size_t)sel * rpad + row] = o;
   if (with_rho) {   // one-pass selection: every block's offset is the row's estimate
     const float r = ok && L > 0.f ? fast_exp2(p[0].x - o) : 0.f;
-    const bool redo = ok && (bad || !(r < INFINITY));
+    const bool redo = ok && (bad || lost || !(r < INFINITY));
     const float rw = max_xor32(max_xor16(r));
     if (__ballot(redo)) {
       if ((threadIdx.x & 63) == 0) atomicOr(&a.redo[sel], 1u);

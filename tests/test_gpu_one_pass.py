@@ -141,3 +141,27 @@ def test_estimates_far_above_the_sums():
         k[head, (n_keys - 32) * t // (SAMPLES - 1) + 5, :2] = 0
     idx, sc = _select_head(q, k, head, 8, 64)
     check_topk(idx, sc, 64)
+
+
+def test_sampled_keys_all_masked():
+    """Keys hidden by a component of -inf: all the sampled ones, so there is
+    nothing to estimate the rows' sums from; the visible ones score -200 in
+    log2 units."""
+    n_keys, head = 262144, 3
+    q, k = _random_heads(8, 16, n_keys + 16, head)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    q[head] = torch.randn((16, 128), generator=g, device=DEV).bfloat16()
+    q[head, :, 0], q[head, :, 1] = 1, 16
+    k[head, :, 0] = -math.inf
+    lo = 135400                                          # 4096 visible keys between two sampled tiles
+    k[head, lo:lo + 4096] = torch.randn((4096, 128), generator=g, device=DEV).bfloat16()
+    k[head, lo:lo + 4096, 0], k[head, lo:lo + 4096, 1] = 0, -98
+    first = torch.arange(SAMPLES) * (n_keys - 32) // (SAMPLES - 1)
+    assert ((first + 32 <= lo) | (first >= lo + 4096)).all()
+    idx = ck.select_critical(q, k, list(range(8)), 8, 64).cpu().numpy()[head]
+    vis = k[head:head + 1, lo:lo + 4096].float().cpu().numpy().astype(np.float64)
+    qf = q[head:head + 1].float().cpu().numpy().astype(np.float64)
+    sc = np.zeros(n_keys // 8)
+    pad = np.concatenate([vis, np.zeros((1, 16, 128))], axis=1)
+    sc[lo // 8:(lo + 4096) // 8] = O.chunk_scores(qf, pad, 0, 1, 16, 8, 1 / math.sqrt(128))
+    check_topk(idx, sc, 64)
