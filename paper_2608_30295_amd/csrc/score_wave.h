@@ -191,8 +191,8 @@ void score_wave_kernel(ScoreArgs a) {
   // kColMass: sums over the 32 lanes of the 32 column sums a lane holds, each
   // lane left with one key's total: row swap, then mirror, half mirror, xor 2
   // and xor 1, halving the values each time.  Lane bits (5..0) then hold key
-  // bits 2, 5, 4, 3, 1, 0.
-  auto finish_cols = [&](int col) {
+  // bits 2, 5, 4, 3, 1, 0.  keys: 32 or 64, the tile's; only theirs are stored.
+  auto finish_cols = [&](int col, int keys) {
     float x[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -210,7 +210,7 @@ void score_wave_kernel(ScoreArgs a) {
     v *= 1.0f / (float)G;
     const int key = (lane & 3) | (half << 2) | ((lane & 12) << 1) | ((lane & 16) << 1);
     const int64_t kc = col0 + col + key;
-    const bool ok = col + key < c_hi;
+    const bool ok = key < keys && col + key < c_hi;
     if (a.cs_fused > 0) {
       const int cs = a.cs_fused;
       float m = ok ? v : -INFINITY;
@@ -320,7 +320,7 @@ void score_wave_kernel(ScoreArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) cm[1][r] = 0.f;
       }
-      finish_cols(col);
+      finish_cols(col, NT2 * 32);
     }
   };
   // ---- the run: 32 keys, full tiles, 32 keys, then the masked rest -----------
