@@ -93,7 +93,7 @@ struct SelectGeom {
   int n_colblk;            // column blocks of the score passes
   int64_t wcb_tokens;      // the same of the bf16 passes (score_wave.h); never more blocks than n_colblk
   int wn_colblk, unit_log;
-  int64_t fcb_tokens;      // the same of the fp32 passes; never fewer blocks than n_colblk
+  int64_t fcb_tokens;      // the same of the fp32 passes
   int fn_colblk;
   int heads[128];
 };
@@ -114,7 +114,8 @@ inline int score_waves(int dtype, int rows_pad) {
 // rows_pad query rows on a device of n_cu compute units; at most
 // kMaxBlockTokens (the kernels address a block's K rows with 32-bit offsets).
 constexpr int64_t kMaxBlockTokens = (int64_t)1 << 22;
-int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu, int min_tiles);
+int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu);
+int64_t score_block_tokens_f32(int64_t n_keys, int n_heads, int rows_pad, int n_cu);
 // bf16 row counts whose passes run on score_wave.h.  512 rows keep the 16-wave
 // workgroups of score.h, whose query rows stay in registers: 31 + 30 us
 // against 36 + 29 at 39939 keys of 4 heads (there the offsets and sums would

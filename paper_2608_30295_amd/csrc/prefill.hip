@@ -865,20 +865,29 @@ __global__ void compact_kernel(CompactArgs a) {
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Score workgroups run in a single round: as many as the device holds at once
 // (the bf16 residency: two workgroups per compute unit, whose LDS rings fill
-// 128 KB of its 160 KB, or one 16-wave workgroup at 512 rows; fp32 beyond 128
-// rows runs in two rounds), each over whole 64-column tiles, at least
-// min_tiles of them and at most kMaxBlockTokens columns (more rounds beyond).
-// bf16 blocks hold at least four tiles.  An fp32 tile is one serial chain of
-// 128 to 512 MFMAs of a sixteenth of the bf16 rate, so there every tile of a
-// short row gets a workgroup: 4064 keys of 4 heads, 128 rows: 24.0 -> 11.5 us
-// per pass against four tiles each.  Workspaces are sized for the larger
-// count, so they do not depend on the dtype.
-int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu, int min_tiles) {
-  const int64_t slots = (int64_t)std::max(1, n_cu) * (score_waves(CATEKV_BF16, rows_pad) > 8 ? 1 : 2);
+// 128 KB of its 160 KB, or one 16-wave workgroup at 512 rows), each over whole
+// 64-column tiles, at least min_tiles of them and at most kMaxBlockTokens
+// columns (more rounds beyond).  Workspaces hold the larger count of the two
+// dtypes, so they do not depend on it.
+static int64_t block_tokens(int64_t n_keys, int n_heads, int64_t slots, int min_tiles) {
   const int64_t per_head = std::max<int64_t>(1, slots / std::max(1, n_heads));
   int64_t cb = (std::max<int64_t>(n_keys, 1) + per_head - 1) / per_head;
   cb = (cb + kTileTok - 1) / kTileTok * kTileTok;
   return std::min<int64_t>(std::max<int64_t>(cb, min_tiles * kTileTok), kMaxBlockTokens);
+}
+int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu) {
+  return block_tokens(n_keys, n_heads, (int64_t)std::max(1, n_cu) * (score_waves(CATEKV_BF16, rows_pad) > 8 ? 1 : 2), 4);
+}
+// fp32: a tile is one serial chain of 128 to 512 MFMAs of a sixteenth of the
+// bf16 rate, so every tile of a short row gets a workgroup (4064 keys of 4
+// heads, 128 rows: 24.0 -> 11.5 us per pass against four tiles each), up to
+// what the device holds at once: beyond 128 rows eight waves of two per SIMD,
+// one workgroup per compute unit.  Blocks for two per unit there ran two
+// rounds where one of blocks twice as long is as much work and one prologue
+// less (256 rows, 1032 tiles of 64 keys: selection 133 -> 107 us; 771 tiles
+// 99 -> 88).
+int64_t score_block_tokens_f32(int64_t n_keys, int n_heads, int rows_pad, int n_cu) {
+  return block_tokens(n_keys, n_heads, (int64_t)std::max(1, n_cu) * (rows_pad > 128 ? 1 : 2), 1);
 }
 
 // One workgroup of score_wave.h per compute unit, in a single round; at least
@@ -899,7 +908,7 @@ static SelectLayout select_layout(const SelectGeom& g) {
   SelectLayout L{};
   const int rp = score_rows_pad(g.G * g.l_obs);
   size_t o = 0;
-  L.rowpart = o; o += align256((size_t)g.n_sel * g.fn_colblk * rp * sizeof(float2));
+  L.rowpart = o; o += align256((size_t)g.n_sel * std::max(g.n_colblk, g.fn_colblk) * rp * sizeof(float2));
   L.rowoff = o; o += align256((size_t)g.n_sel * rp * sizeof(float));
   // per-key column mass only when BlockMax cannot be fused into the score pass
   // (cs not dividing the 64-column tile)
@@ -1172,7 +1181,7 @@ static ScoreLayout score_layout(const ScoreGeom& g) {
   ScoreLayout L{};
   const int rp = score_rows_pad(g.G * g.lq);
   size_t o = 0;
-  L.rowpart = o; o += align256((size_t)g.hkv * g.fn_colblk * rp * sizeof(float2));
+  L.rowpart = o; o += align256((size_t)g.hkv * std::max(g.n_colblk, g.fn_colblk) * rp * sizeof(float2));
   L.rowoff = o; o += align256((size_t)g.hkv * rp * sizeof(float));
   L.obs = o; o += align256((size_t)g.hkv * g.lq * g.n_keys * sizeof(float));
   L.cv = o; o += align256(std::max(cv_workspace_bytes(g.hkv, g.lq, g.n_keys, g.n_colblk),

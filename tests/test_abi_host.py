@@ -261,3 +261,38 @@ def test_retrieval_rejects_bad_arguments():
     rc, _ = _status_and_msg(L.catekv_retrieve_pages(1, FAKE, FAKE, FAKE, 8, 2, 13, 128, heads, 1, 4, FAKE, FAKE,
                                                     need - 256, None))
     assert rc == _lib.CATEKV_ERR_WORKSPACE
+
+
+# ------------------------------------------------- column blocks of the score passes, from the workspace's size
+
+def _a256(x):
+    return (x + 255) // 256 * 256
+
+
+def _select_blocks(rows, n_keys, cs, n_sel):
+    """Column blocks per head that the selection's row statistics are laid out for (fp32's, the most)."""
+    G = 4
+    n_chunks = -(-n_keys // cs)
+    rp = next(p for p in (64, 128, 256, 512) if rows <= p)
+    ws = ck.select_workspace(8 * G, 8, rows // G, n_keys + rows // G, cs, n_sel)
+    ws -= _a256(n_sel * rp * 4) + _a256(n_sel * n_chunks * 4)                        # offsets, chunk scores
+    ws -= _a256(_a256(n_sel * 4) + (n_sel * 2 * 16384 * 8 if n_chunks > 4096 else 0))   # top-k
+    assert ws % (n_sel * rp * 8) == 0
+    return ws // (n_sel * rp * 8)
+
+
+@pytest.mark.parametrize("rows", [32, 64, 128, 256, 512])
+@pytest.mark.parametrize("n_sel", [1, 3, 7, 8])
+def test_fp32_blocks_fill_one_round(rows, n_sel):
+    """fp32 score workgroups stay resident at once until each has four tiles
+    of 64 keys: two per compute unit up to 128 rows, one beyond (256 units:
+    this container has none, so the library assumes an MI355X)."""
+    held = 256 * (1 if rows > 128 else 2)
+    for n_keys in [64, 100, 1000, 4064, 8136, 10340, 16336, 20000, 32936]:
+        blocks, tiles = _select_blocks(rows, n_keys, 8, n_sel), -(-n_keys // 64)
+        per_head = held // n_sel
+        if tiles <= per_head:
+            assert blocks == tiles, (n_keys, blocks)                 # a tile each
+        elif tiles <= 4 * per_head:
+            assert blocks <= per_head, (n_keys, blocks)              # one round
+        assert blocks * 4 >= min(tiles, per_head), (n_keys, blocks)
