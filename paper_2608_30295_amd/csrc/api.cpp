@@ -384,6 +384,15 @@ int catekv_select_critical_noalloc(int dtype, const void* q_obs, const void* k, 
   return ok();
 }
 
+// For the tests (not declared in catekv.h): which passes a call runs on
+// (ScoreRoute), so that a case can be shown to take the route it is meant for.
+int catekv_select_route(int dtype, int hq, int hkv, int l_obs, int64_t n, int cs, int n_sel, int b) {
+  return catekv::select_route(dtype, select_geom(hq, hkv, l_obs, n, cs, nullptr, n_sel, b));
+}
+int catekv_score_route(int dtype, int hq, int hkv, int lq, int64_t n, int64_t l_init, int64_t l_rec) {
+  return catekv::score_route(dtype, score_geom(hq, hkv, lq, n, l_init, l_rec));
+}
+
 int catekv_compact_kv(int dtype, const void* k, const void* v, int hkv, int64_t n, int d, int cs,
                       int l_obs, const int32_t* sel_heads_host, int n_sel, const int32_t* idx, int b,
                       void* k_c, void* v_c, int64_t* lens_out, void* stream) {

@@ -91,7 +91,7 @@ struct SelectGeom {
   int64_t n_chunks;
   int64_t cb_tokens;       // key columns per score workgroup
   int n_colblk;            // column blocks of the score passes
-  int64_t wcb_tokens;      // the same of the bf16 passes (score_wave.h); never more blocks than n_colblk
+  int64_t wcb_tokens;      // the same of the passes of score_wave.h; never more blocks than n_colblk
   int wn_colblk, unit_log;
   int64_t fcb_tokens;      // the same of the fp32 passes
   int fn_colblk;
@@ -116,8 +116,8 @@ inline int score_waves(int dtype, int rows_pad) {
 constexpr int64_t kMaxBlockTokens = (int64_t)1 << 22;
 int64_t score_block_tokens(int64_t n_keys, int n_heads, int rows_pad, int n_cu);
 int64_t score_block_tokens_f32(int64_t n_keys, int n_heads, int rows_pad, int n_cu);
-// bf16 row counts whose passes run on score_wave.h.  512 rows keep the 16-wave
-// workgroups of score.h, whose query rows stay in registers: 31 + 30 us
+// bf16 row counts that score_wave.h has builds for.  512 rows run on the
+// 16-wave workgroups of score.h, whose query rows stay in registers: 31 + 30 us
 // against 36 + 29 at 39939 keys of 4 heads (there the offsets and sums would
 // not fit the registers, and the query rows take 139 KB of LDS).
 inline bool score_wave_rows(int rows_pad) { return rows_pad < 512; }
@@ -125,6 +125,10 @@ inline bool score_wave_rows(int rows_pad) { return rows_pad < 512; }
 // 1 << unit_log keys.
 int64_t score_wave_block_tokens(int64_t n_keys, int n_heads, int unit_log, int n_cu);
 size_t select_workspace_bytes(const SelectGeom& g);
+// How a call's passes run: two passes of score.h or of score_wave.h, or
+// (selection) one pass of score_wave.h and the candidates.
+enum ScoreRoute { kRouteTile = 0, kRouteWave = 1, kRouteOnePass = 2 };
+ScoreRoute select_route(int dtype, const SelectGeom& g);
 // The file-scope scratch of the allocation-free selection: its size, and its
 // device address on the current device.
 size_t select_scratch_bytes();
@@ -164,6 +168,7 @@ struct ScoreGeom {
 };
 
 size_t score_workspace_bytes(const ScoreGeom& g);
+ScoreRoute score_route(int dtype, const ScoreGeom& g);   // of the row statistics
 
 hipError_t launch_score(int dtype, const ScoreGeom& g, const void* q_rows, const void* k,
                         float* cv_out, void* ws, hipStream_t stream);

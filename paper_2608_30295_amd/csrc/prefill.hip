@@ -901,6 +901,24 @@ int64_t score_wave_block_tokens(int64_t n_keys, int n_heads, int unit_log, int n
   return std::min<int64_t>(std::max<int64_t>(cb, 8 << unit_log), kMaxBlockTokens);
 }
 
+// Whether bf16 passes of up to 256 rows over n_heads heads run on
+// score_wave.h (blocks of wcb_tokens keys) or on score.h.  A pass of
+// score_wave.h starts 3 us later (the query rows go to LDS before the first
+// keys are requested, and a wave's 32-key steps are code of their own), which
+// it makes up once its waves have enough keys: above 2.5 units of 32 up to 128
+// rows (64 rows, 3 heads: both passes 6.5 us longer at 49152 keys in all, 3.3
+// at 131072, 2.7 shorter at 180000, 5.3 at 1048576; 128 rows 5.8 and 1.2
+// longer, 3.3 and 10.0 shorter), above one unit at 256 (1.6 us longer at 49152
+// keys, 2.9 shorter at 65536).
+static bool wave_run(int rows_pad, int64_t wcb_tokens) {
+  return score_wave_rows(rows_pad) && wcb_tokens > kSwWaves * (rows_pad > 128 ? 32 : 80);
+}
+// Two passes of up to 64 rows over more K than the last-level cache holds
+// (256 MB: 2^20 keys) are bound by HBM alone, where the 16 KB tiles of
+// score.h are read 1% faster on average (25 shapes of 1.3M to 4.9M keys: 7.9%
+// to -0.5%); at 1M keys of one head score_wave.h is 5.6% faster.
+constexpr int64_t kTileReread = (int64_t)5 << 18;
+
 struct SelectLayout {
   size_t rowpart, rowoff, colmass, chunks, topk, total;
 };
@@ -984,6 +1002,14 @@ static OnePass one_pass(const SelectGeom& g, const SelectLayout& L) {
   return p;
 }
 
+ScoreRoute select_route(int dtype, const SelectGeom& g) {
+  const int rp = score_rows_pad(g.G * g.l_obs);
+  if (dtype != CATEKV_BF16) return kRouteTile;
+  if (one_pass(g, select_layout(g)).n_cand > 0) return kRouteOnePass;
+  if (rp <= 64 && g.n_sel * g.n_keys > kTileReread) return kRouteTile;
+  return wave_run(rp, g.wcb_tokens) ? kRouteWave : kRouteTile;
+}
+
 hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, const void* k,
                          int32_t* idx_out, void* ws, hipStream_t stream) {
   const SelectLayout L = select_layout(g);
@@ -994,8 +1020,8 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
   a.q = q_obs; a.k = k; a.hkv = g.hkv; a.lq = g.l_obs; a.G = g.G; a.R = R; a.n = g.n;
   const bool bf = dtype == CATEKV_BF16;
   a.key_off = 0; a.n_keys = g.n_keys;
-  const OnePass op = bf ? one_pass(g, L) : OnePass{};
-  const bool wave = bf && score_wave_rows(rp);
+  const ScoreRoute route = select_route(dtype, g);
+  const bool wave = route != kRouteTile;
   a.cb_tokens = wave ? g.wcb_tokens : bf ? g.cb_tokens : g.fcb_tokens;
   a.n_colblk = wave ? g.wn_colblk : bf ? g.n_colblk : g.fn_colblk;
   a.rp = rp; a.unit_log = g.unit_log;
@@ -1015,7 +1041,8 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
   const dim3 mgrid((rp + kMergeRows - 1) / kMergeRows, g.n_sel), cgrid((unsigned)((g.n_chunks + 255) / 256), g.n_sel);
   float* off = reinterpret_cast<float*>(w + L.rowoff);
   hipError_t e;
-  if (op.n_cand > 0) {
+  if (route == kRouteOnePass) {
+    const OnePass op = one_pass(g, L);
     float* est = reinterpret_cast<float*>(w + op.est);
     uint32_t* redo = reinterpret_cast<uint32_t*>(w + op.words) + g.n_sel;
     int32_t* cand = reinterpret_cast<int32_t*>(w + op.cand);
@@ -1071,12 +1098,12 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
 #undef CATEKV_FIN
     a.gate = redo;
   } else {
-    e = launch_score_rowstats(dtype, g.G, false, rp, grid, stream, a);
+    e = launch_score_rowstats(dtype, wave, g.G, false, rp, grid, stream, a);
     if (e != hipSuccess) return e;
     if (dtype == CATEKV_BF16) hipLaunchKernelGGL((rowstats_merge_kernel<uint16_t, kMergeThreads>), mgrid, dim3(kMergeThreads), 0, stream, a, rp, off);
     else hipLaunchKernelGGL((rowstats_merge_kernel<float, kMergeThreads>), mgrid, dim3(kMergeThreads), 0, stream, a, rp, off);
   }
-  e = launch_score_colmass(dtype, rp, grid, stream, a);
+  e = launch_score_colmass(dtype, wave, rp, grid, stream, a);
   if (e != hipSuccess) return e;
   if (!a.cs_fused)
     hipLaunchKernelGGL(chunk_max_kernel, cgrid, dim3(256), 0, stream, a.colmass, g.n_keys, g.cs, g.n_chunks, S, a.gate);
@@ -1198,6 +1225,11 @@ static int obs_waves(int dtype, int G, int rows_pad) {
   return G == 1 ? std::min(score_waves(dtype, rows_pad), 8) : score_waves(dtype, rows_pad);
 }
 
+ScoreRoute score_route(int dtype, const ScoreGeom& g) {
+  const int rp = score_rows_pad(g.G * g.lq);
+  return dtype == CATEKV_BF16 && wave_run(rp, g.wcb_tokens) ? kRouteWave : kRouteTile;
+}
+
 hipError_t launch_score(int dtype, const ScoreGeom& g, const void* q_rows, const void* k,
                         float* cv_out, void* ws, hipStream_t stream) {
   const ScoreLayout L = score_layout(g);
@@ -1217,13 +1249,14 @@ hipError_t launch_score(int dtype, const ScoreGeom& g, const void* q_rows, const
   a.rowoff = reinterpret_cast<const float*>(w + L.rowoff);
   a.obs = reinterpret_cast<float*>(w + L.obs);
   a.cv = cv_link(w + L.cv, g.hkv, g.lq, g.n_keys, a.n_colblk, obs_waves(dtype, g.G, rp));
-  ScoreArgs r = a;          // row statistics: the blocks of the bf16 pass
-  if (bf && score_wave_rows(rp)) {
+  ScoreArgs r = a;          // row statistics: the blocks of their pass
+  const bool wave = score_route(dtype, g) == kRouteWave;
+  if (wave) {
     r.cb_tokens = g.wcb_tokens;
     r.n_colblk = g.wn_colblk;
   }
   const dim3 grid(a.n_colblk, g.hkv);
-  hipError_t e = launch_score_rowstats(dtype, g.G, g.causal, rp, dim3(r.n_colblk, g.hkv), stream, r);
+  hipError_t e = launch_score_rowstats(dtype, wave, g.G, g.causal, rp, dim3(r.n_colblk, g.hkv), stream, r);
   if (e != hipSuccess) return e;
   if (dtype == CATEKV_BF16)
     hipLaunchKernelGGL((rowstats_merge_kernel<uint16_t, kMergeThreadsCv>), dim3((rp + kMergeRows - 1) / kMergeRows, g.hkv),

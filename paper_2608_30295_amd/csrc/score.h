@@ -9,8 +9,9 @@
 //           observation matrix A[i][j] (CV).
 // Workgroup = 4 to 16 waves sharing one 64-token K tile staged in LDS; wave w
 // owns rows [w * MT * 16, (w + 1) * MT * 16) with their Q fragments in
-// registers.  fp32, 512 rows and the observation passes run here; bf16 row
-// statistics and column mass up to 256 rows in score_wave.h.
+// registers.  fp32, 512 rows, the observation passes and short rows of keys
+// run here; bf16 row statistics and column mass over long rows, up to 256
+// query rows, in score_wave.h (select_route and score_route say which).
 // Each pass is instantiated in a source file of its own (score_*.hip).
 #pragma once
 
@@ -618,10 +619,11 @@ inline hipError_t launch_score_mt(int rows_pad, dim3 grid, hipStream_t s, const 
 }
 
 // Launch one score pass over grid (column blocks, heads) for rows_pad query
-// rows (64, 128, 256 or 512; see score_waves).
-hipError_t launch_score_rowstats(int dtype, int G, bool causal, int rows_pad, dim3 grid, hipStream_t s,
+// rows (64, 128, 256 or 512; see score_waves).  wave: on score_wave.h (bf16,
+// up to 256 rows).
+hipError_t launch_score_rowstats(int dtype, bool wave, int G, bool causal, int rows_pad, dim3 grid, hipStream_t s,
                                  const ScoreArgs& a);
-hipError_t launch_score_colmass(int dtype, int rows_pad, dim3 grid, hipStream_t s, const ScoreArgs& a);
+hipError_t launch_score_colmass(int dtype, bool wave, int rows_pad, dim3 grid, hipStream_t s, const ScoreArgs& a);
 // bf16 (score_wave.h): row sums against given offsets and column mass in one
 // pass, and the column mass of gathered chunks
 hipError_t launch_score_both(dim3 grid, hipStream_t s, const ScoreArgs& a);

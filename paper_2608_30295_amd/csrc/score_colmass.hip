@@ -6,13 +6,10 @@
 
 namespace catekv {
 
-hipError_t launch_score_colmass(int dtype, int rows_pad, dim3 grid, hipStream_t s, const ScoreArgs& a) {
-  if (dtype == CATEKV_BF16) {
-    if (score_wave_rows(rows_pad)) return launch_score_wave<kColMass>(grid, s, a);
-    hipLaunchKernelGGL((score_kernel<uint16_t, 16, 2, kColMass, 0, false, 4>), grid, dim3(1024), 0, s, a);
-    return hipGetLastError();
-  }
-  return launch_score_mt<float, kColMass, 0, false>(rows_pad, grid, s, a);
+hipError_t launch_score_colmass(int dtype, bool wave, int rows_pad, dim3 grid, hipStream_t s, const ScoreArgs& a) {
+  if (wave) return launch_score_wave<kColMass>(grid, s, a);
+  return dtype == CATEKV_BF16 ? launch_score_mt<uint16_t, kColMass, 0, false>(rows_pad, grid, s, a)
+                              : launch_score_mt<float, kColMass, 0, false>(rows_pad, grid, s, a);
 }
 
 hipError_t launch_score_both(dim3 grid, hipStream_t s, const ScoreArgs& a) { return launch_score_wave<kBoth>(grid, s, a); }

@@ -1,5 +1,5 @@
-// Score passes of the prefill kernels for bf16 (the fp32 passes are in
-// score.h, which also says what a pass computes).  What bounds them is the
+// Score passes of the prefill kernels for bf16 over long rows of keys (the
+// others are in score.h, which also says what a pass computes).  What bounds them is the
 // matrix core together with the softmax arithmetic (one fma, one exp2 and one
 // add per score) and, up to 128 query rows, HBM; so nothing else may stand in
 // the way of the three running side by side:

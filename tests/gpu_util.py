@@ -2,12 +2,31 @@
 the parity comparisons (tolerances from the paper-path contract: bf16 inputs
 with fp32 accumulation must match the fp64 oracle within max-abs 2e-3 and
 relative L2 1e-3; fp32 inputs within 1e-5)."""
+import ctypes
+
 import numpy as np
 import torch
 
+import paper_2608_30295_amd as ck
 import synth
 
 DEV = "cuda:0"
+
+
+# passes of a call: csrc/internal.h, ScoreRoute
+TILE, WAVE, ONE_PASS = 0, 1, 2
+
+
+def select_route(hq: int, hkv: int, l_obs: int, n: int, cs: int, n_sel: int, b: int, bf16: bool = True) -> int:
+    f = ck.lib().catekv_select_route
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.c_int64] + [ctypes.c_int] * 3
+    return f(int(bf16), hq, hkv, l_obs, n, cs, n_sel, b)
+
+
+def score_route(hq: int, hkv: int, lq: int, n: int, l_init: int, l_rec: int, bf16: bool = True) -> int:
+    f = ck.lib().catekv_score_route
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.c_int64] * 3
+    return f(int(bf16), hq, hkv, lq, n, l_init, l_rec)
 
 
 def to_dev(st: np.ndarray) -> torch.Tensor:
