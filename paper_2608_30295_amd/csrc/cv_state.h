@@ -13,13 +13,21 @@ constexpr uint32_t kCvNone = 0xFFFFFFFFu;
 constexpr int kCvListCap = 65536;             // entries of x_(lo)'s first-digit bin listed, at most
 constexpr int kCvMaxSub = 16;                 // waves per score workgroup, at most
 
-// The sample of A that brackets the quantile: 1024 runs of 8 consecutive
-// entries spread evenly over the N entries (all of them when N <= 8192).
-// Sample s = 8 t + u is entry t * stride + u in row-major order.
-constexpr int kCvSampleRuns = 1024, kCvSampleRun = 8, kCvSamples = kCvSampleRuns * kCvSampleRun;
+// The sample of A that brackets the quantile: 8192 of the N entries (all of
+// them when there are fewer), spread evenly over the rows, and over the columns
+// by multiples of the golden ratio: neighbouring keys, and one key seen by
+// several queries, score alike, so that entries have to be of different keys
+// and not of neighbours to count as independent.  Runs of eight neighbours a
+// fixed number of entries apart fell on the same 128 keys in every row where
+// the key count was a power of two.
+constexpr int kCvSamples = 8192, kCvSampleLog = 13;
 __host__ __device__ inline int64_t cv_sample_count(int64_t N) { return N < kCvSamples ? N : kCvSamples; }
-__host__ __device__ inline int64_t cv_sample_stride(int64_t N) {
-  return N < kCvSamples ? kCvSampleRun : (N / kCvSampleRuns) & ~(int64_t)(kCvSampleRun - 1);
+// row and column of sample s of lq rows and n_keys columns
+__device__ __forceinline__ uint32_t cv_sample_row(uint32_t s, uint32_t lq, uint32_t n_keys) {
+  return lq * (uint64_t)n_keys < kCvSamples ? s / n_keys : (s * lq) >> kCvSampleLog;
+}
+__device__ __forceinline__ uint32_t cv_sample_col(uint32_t s, uint32_t lq, uint32_t n_keys) {
+  return lq * (uint64_t)n_keys < kCvSamples ? s % n_keys : __umulhi(s * 2654435769u, n_keys);
 }
 
 // Ordered integer key of a float: key order is float order (-0 < +0).

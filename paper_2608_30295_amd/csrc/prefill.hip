@@ -77,21 +77,14 @@ __device__ void cv_sample_rows(const ScoreArgs& a, int sel, int row0, float my_o
   __syncthreads();
   const int q0 = row0 / G, q1 = min(a.lq, (row0 + kMergeRows) / G);   // this workgroup's queries
   if (q0 >= q1) return;
-  const int64_t ns = cv_sample_count(N), stride = cv_sample_stride(N);
+  // the samples of rows q0 to q1 - 1
   const bool all = N < kCvSamples;                                   // sample s is entry s
-  const int64_t e0 = (int64_t)q0 * n_keys, e1 = (int64_t)q1 * n_keys;
-  // (plain selects: std::min / std::max return references, which the
-  // compiler would keep in scratch memory here)
-  const int64_t t0 = (e0 - (kCvSampleRun - 1) + stride - 1) / stride;
-  const int64_t s0 = all ? e0 : (t0 > 0 ? t0 : 0) * kCvSampleRun;
-  const int64_t s1r = all ? e1 : ((e1 - 1) / stride + 1) * kCvSampleRun;
-  const int64_t s1 = s1r < ns ? s1r : ns;
+  auto first = [&](int q) { return all ? (uint32_t)q * n_keys : (uint32_t)((q * kCvSamples + a.lq - 1) / a.lq); };
+  const uint32_t s0 = first(q0), s1 = first(q1);
   const T* kh = reinterpret_cast<const T*>(a.k) + (size_t)h * a.n * kD;
   const float invG = 1.0f / (float)G;
-  for (int64_t s = s0 + t; s < s1; s += NT) {
-    const uint32_t ent = (uint32_t)(all ? s : (s / kCvSampleRun) * stride + (s % kCvSampleRun));
-    const uint32_t i = ent / n_keys, j = ent - (ent / n_keys) * n_keys;
-    if ((int)i < q0 || (int)i >= q1) continue;
+  for (uint32_t s = s0 + t; s < s1; s += NT) {
+    const uint32_t i = cv_sample_row(s, a.lq, n_keys), j = cv_sample_col(s, a.lq, n_keys);
     const float* qr = s_q[(i - q0) * G];
     const T* kr = kh + (size_t)(a.key_off + j) * kD;
     float dot[G];
