@@ -389,6 +389,11 @@ int catekv_select_critical_noalloc(int dtype, const void* q_obs, const void* k, 
 int catekv_select_route(int dtype, int hq, int hkv, int l_obs, int64_t n, int cs, int n_sel, int b) {
   return catekv::select_route(dtype, select_geom(hq, hkv, l_obs, n, cs, nullptr, n_sel, b));
 }
+// Offset in the workspace of n_sel 32-bit words, nonzero for the heads that a
+// one-pass selection had to score in full; 0 if the call takes two passes.
+size_t catekv_select_redone(int dtype, int hq, int hkv, int l_obs, int64_t n, int cs, int n_sel, int b) {
+  return catekv::select_redone(dtype, select_geom(hq, hkv, l_obs, n, cs, nullptr, n_sel, b));
+}
 int catekv_score_route(int dtype, int hq, int hkv, int lq, int64_t n, int64_t l_init, int64_t l_rec) {
   return catekv::score_route(dtype, score_geom(hq, hkv, lq, n, l_init, l_rec));
 }

@@ -129,6 +129,7 @@ size_t select_workspace_bytes(const SelectGeom& g);
 // (selection) one pass of score_wave.h and the candidates.
 enum ScoreRoute { kRouteTile = 0, kRouteWave = 1, kRouteOnePass = 2 };
 ScoreRoute select_route(int dtype, const SelectGeom& g);
+size_t select_redone(int dtype, const SelectGeom& g);
 // The file-scope scratch of the allocation-free selection: its size, and its
 // device address on the current device.
 size_t select_scratch_bytes();

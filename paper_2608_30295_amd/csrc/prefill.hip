@@ -167,7 +167,7 @@ __device__ __forceinline__ float merge_row(const ScoreArgs& a, int rpad, float* 
     M = mb;
   }
   // One-pass selection: every block's sum is taken against the row's estimate,
-  // which is at most n_keys / 128 times the sum (2^24: n_keys < 2^31) where it
+  // which is at most n_keys / 896 times the sum (2^22: n_keys < 2^31) where it
   // is one.  A sum further below has no estimate behind it (the sampled scores
   // were all -inf) and may have vanished: its blocks are all recomputed.
   const float rsum = sum16(L);
@@ -367,7 +367,9 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(const float* __restr
 // entries of its own slice is outranked by k entries of the row; ties go to
 // the lower index in both), and the candidate list is ascending, so the two
 // stages reproduce the one-stage result.
-enum TopkMode { kTopkRow = 0, kTopkSliceMode = 1, kTopkList = 2 };
+// kTopkHeld: entry e of list_len candidates is the caller's, in held[i] of the
+// lane that topk_entry() names.
+enum TopkMode { kTopkRow = 0, kTopkSliceMode = 1, kTopkList = 2, kTopkHeld = 3 };
 constexpr int64_t kTopkSlice = 16 * kTopkThreads;   // scores per slice of long rows
 constexpr int64_t kTopkSmallSlice = 4 * kTopkThreads;   // scores per slice of short rows
 
@@ -383,8 +385,8 @@ struct TopkArgs {
   int64_t n;
   const TopkCand* list;    // kTopkList: candidates [rows][list_len]
   int64_t list_len;
-  int k, b;                // select k; kTopkRow / kTopkList write b entries per row (-1 padded)
-  int32_t* out;            // kTopkRow / kTopkList: [rows][b]
+  int k, b;                // select k; all but kTopkSliceMode write b entries per row (-1 padded)
+  int32_t* out;            // all but kTopkSliceMode: [rows][b]
   TopkCand* cand;          // kTopkSliceMode: [rows][n_slices][k]
   const uint32_t* gate;    // rows with a zero word are left alone (null: none)
 };
@@ -429,8 +431,16 @@ __device__ __forceinline__ int wave_suffix_sum(int x) {
   return x + (row < 1 ? r1 : 0) + (row < 2 ? r2 : 0) + (row < 3 ? r3 : 0);
 }
 
+// the entry of a lane's row i
+template <int PER>
+__device__ __forceinline__ int64_t topk_entry(int i) {
+  return (int64_t)(threadIdx.x >> 6) * PER * 64 + (threadIdx.x & 63) + 64 * i;
+}
+
 template <int PER, int MODE>
-__device__ __forceinline__ uint32_t topk_body(const TopkArgs& a, int row, int slice, int n_slices) {
+__device__ __forceinline__ uint32_t topk_body(const TopkArgs& a, int row, int slice, int n_slices,
+                                              const TopkCand* held = nullptr) {
+  constexpr bool LIST = MODE == kTopkList || MODE == kTopkHeld;
   constexpr int NW = kTopkThreads / 64;
   constexpr int NCOPY = 16;
   constexpr int RS = 260;                  // words per copy: 256 bins, rows 16-byte aligned
@@ -456,15 +466,16 @@ __device__ __forceinline__ uint32_t topk_body(const TopkArgs& a, int row, int sl
     k = (int)min((int64_t)a.k, len);
     b = a.k;
     cout = a.cand + ((size_t)row * n_slices + slice) * a.k;
-  } else if (MODE == kTopkList) {
+  } else if (LIST) {
     len = a.list_len;
-    lst = a.list + (size_t)row * a.list_len;
+    if (MODE == kTopkList) lst = a.list + (size_t)row * a.list_len;
   }
-  const int64_t base = (int64_t)wave * PER * 64 + lane;       // entry of row 0; row i adds 64 i
+  const int64_t base = topk_entry<PER>(0);
   // kTopkList keeps the candidates' indices in registers up to 8 per lane
   // and reads longer lists' indices again when writing (registers: at most
   // 128 per lane at 1024 threads)
   constexpr bool KEEP = PER <= 8;
+  static_assert(KEEP || MODE != kTopkHeld, "held candidates keep their indices");
   uint32_t key[PER];
   int32_t idx[KEEP ? PER : 1];
   uint32_t vmask = 0;                                          // bit i: row i holds an entry
@@ -476,8 +487,8 @@ __device__ __forceinline__ uint32_t topk_body(const TopkArgs& a, int row, int sl
     const int64_t e = base + 64 * i;
     const bool in = e < len;
     const int64_t ec = in ? e : last;
-    if (MODE == kTopkList) {
-      const TopkCand c = __hip_atomic_load(&lst[ec], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (LIST) {
+      const TopkCand c = MODE == kTopkHeld ? held[i] : __hip_atomic_load(&lst[ec], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int32_t j = in ? (int32_t)(c >> 32) : -1;
       if (KEEP) idx[KEEP ? i : 0] = j;
       key[i] = j >= 0 ? (uint32_t)c : 0u;
@@ -625,7 +636,7 @@ __device__ __forceinline__ uint32_t topk_body(const TopkArgs& a, int row, int sl
     const int p = pos + __popcll(mt & below);
     if (take && p < k) {
       const int64_t e = base + 64 * i;
-      if (MODE == kTopkList)
+      if (LIST)
         out[p] = KEEP ? idx[KEEP ? i : 0]
                       : (int32_t)(__hip_atomic_load(&lst[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32);
       else if (MODE == kTopkSliceMode)
@@ -673,12 +684,12 @@ __global__ __launch_bounds__(kTopkThreads) void topk_fused_kernel(TopkArgs s1, T
 // One-pass selection (bf16, long rows of keys, small budgets).  The column
 // mass needs every row's sum first, which took a pass of its own over K
 // (q.k again, K from HBM again).  Here the pass that sums the rows also adds
-// up the columns, with each row weighted by an estimate of its sum from 1024
+// up the columns, with each row weighted by an estimate of its sum from 8192
 // sampled keys instead of the sum itself: C'_j = sum_i rho_i^-1 w_i e_ij for
 // the true weights w_i, where rho_i = estimate / sum is known afterwards.  So
 // C_j <= max(rho) C'_j, and the chunks that can be among the b best are those
 // whose C' reaches C_(b) / max(rho):
-//   row_estimate_kernel   estimates
+//   score pass kRowEst    estimates
 //   score pass kBoth      row sums and chunk maxima of C'
 //   merge                 exact row offsets, max(rho)
 //   top-k                 the n_cand best chunks by C'
@@ -686,63 +697,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_fused_kernel(TopkArgs s1, T
 //   select_final_kernel   the b best of them, and the proof: the smallest C'
 //                         among the candidates times max(rho) lies below the
 //                         b-th exact score, so no other chunk can reach it
-// A head without that proof (flat scores, or row sums that are not finite)
-// is redone with the full column-mass pass, whose launches return at once
+// A head without that proof (near-equal scores, a few unsampled keys with most
+// of the mass, or row sums that are not finite) is redone with the full column-mass pass, whose launches return at once
 // for the others.
 // ---------------------------------------------------------------------------
-
-// The sum of exp2(s c) of a row over all keys, log2, from each of eight groups
-// of 128 sampled keys; sw_est_pick() takes the third smallest of the eight, so
-// that a few very large terms in some groups do not lift it (rho <= 1 costs
-// nothing; rho >> 1 weakens the bound).  Some group has a sum at least the
-// estimate's, so rho is at most n_keys / 128.  One workgroup per (32 rows,
-// head, group), one tile of 32 keys per wave: latency-bound, so the 64 to 256
-// KB of a head's sample are spread over as many compute units as there are
-// (eight waves of eight tiles each took 20 us).
-__global__ __launch_bounds__(256) void row_estimate_kernel(ScoreArgs a, float* __restrict__ est) {
-  __shared__ float2 s_e[4][32];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = lane & 31, half = lane >> 5;
-  const int sel = blockIdx.y, h = a.heads[sel], grp = blockIdx.z;
-  const int row = blockIdx.x * 32 + n;
-  if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) {
-    a.rho[sel] = 0;
-    a.redo[sel] = 0;
-  }
-  // tiles of 32 keys spread evenly over the keys, dealt to the groups in turn
-  const int64_t key = (a.n_keys - 32) * (wave * kSwEstGroups + grp) / (4 * kSwEstGroups - 1) + n;
-  const char* kr = reinterpret_cast<const char*>(a.k) +
-                   ((size_t)h * a.n + (size_t)(a.key_off + key)) * (kD * 2) + half * 16;
-  const int rc = min(row, a.R - 1), i = rc >> a.g_log, g = rc & (a.G - 1);
-  const char* q = reinterpret_cast<const char*>(a.q) + ((size_t)(h * a.G + g) * a.lq + i) * (kD * 2) + half * 16;
-  uint4 bf[8], kf[8];
-#pragma unroll
-  for (int ks = 0; ks < 8; ++ks) bf[ks] = ldg16(q + ks * 32);
-#pragma unroll
-  for (int ks = 0; ks < 8; ++ks) kf[ks] = ldg16(kr + ks * 32);
-  floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-  for (int ks = 0; ks < 8; ++ks)
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[ks]), __builtin_bit_cast(bf16x8, bf[ks]),
-                                                  acc, 0, 0, 0);
-  float m = acc[0], l = 0.f;
-#pragma unroll
-  for (int r = 1; r < 16; ++r) m = fmaxf(m, acc[r]);
-  m = fmaxf(kMInit, max_xor32(m) * a.c);
-#pragma unroll
-  for (int r = 0; r < 16; ++r) l += fast_exp2(__builtin_fmaf(acc[r], a.c, -m));
-  l = add_xor32(l);
-  if (half == 0) s_e[wave][n] = make_float2(m, l);
-  __syncthreads();
-  if (threadIdx.x < 32 && row < a.R) {
-    float M = kMInit, L = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) M = fmaxf(M, s_e[w][n].x);
-#pragma unroll
-    for (int w = 0; w < 4; ++w) L += s_e[w][n].y * fast_exp2(s_e[w][n].x - M);
-    est[((size_t)sel * a.rp + row) * kSwEstGroups + grp] = M + __log2f(L * ((float)a.n_keys * (1.0f / 128)));
-  }
-}
 
 // The row-statistics merge and, in workgroups of their own, the candidates'
 // top-k: neither needs the other, and side by side they take the top-k's time
@@ -768,30 +726,33 @@ void merge_topk_kernel(ScoreArgs a, int rpad, float* __restrict__ off, TopkArgs 
 // normal number at least.  So has a row's term of a weighted mass: each of
 // the rows may have lost as much there (rho > 1: its exact term need not be
 // that small), and once more in the mean over the group.
+// mass: the candidates' exact scores, or (cs > 1) of the keys of each.
 template <int PER>
-__global__ __launch_bounds__(kTopkThreads) void select_final_kernel(TopkArgs t, TopkCand* __restrict__ list,
-                                                                    const int32_t* __restrict__ cand,
+__global__ __launch_bounds__(kTopkThreads) void select_final_kernel(TopkArgs t, const int32_t* __restrict__ cand,
                                                                     const float* __restrict__ mass, int cs, int64_t n_keys,
                                                                     const float* __restrict__ S, int64_t n_chunks,
                                                                     const uint32_t* __restrict__ rho, int rows, uint32_t* redo) {
   __shared__ float s_min[kTopkThreads / 64];
   const int sel = blockIdx.x, nc = (int)t.list_len;
-  TopkCand* ls = list + (size_t)sel * nc;
+  int32_t ix[PER];
+  TopkCand held[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) ix[i] = cand[(size_t)sel * nc + min((int)topk_entry<PER>(i), nc - 1)];
   float lowest = INFINITY;
-  for (int c = threadIdx.x; c < nc; c += kTopkThreads) {
-    const int32_t ix = cand[(size_t)sel * nc + c];
-    const int len = (int)min((int64_t)cs, n_keys - (int64_t)ix * cs);
-    const float* ms = mass + ((size_t)sel * nc + c) * cs;
-    float m = -INFINITY;
-    for (int j = 0; j < len; ++j) m = fmaxf(m, ms[j]);
-    __hip_atomic_store(&ls[c], ((TopkCand)(uint32_t)ix << 32) | ord_key(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    lowest = fminf(lowest, S[(size_t)sel * n_chunks + ix]);
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    lowest = fminf(lowest, S[(size_t)sel * n_chunks + ix[i]]);
+    const float* ms = mass + ((size_t)sel * nc + min((int)topk_entry<PER>(i), nc - 1)) * cs;
+    float m = cs > 1 ? -INFINITY : ms[0];
+    if (cs > 1) {
+      const int len = (int)min((int64_t)cs, n_keys - (int64_t)ix[i] * cs);
+      for (int j = 0; j < len; ++j) m = fmaxf(m, ms[j]);
+    }
+    held[i] = ((TopkCand)(uint32_t)ix[i] << 32) | ord_key(m);
   }
   for (int off = 32; off > 0; off >>= 1) lowest = fminf(lowest, __shfl_xor(lowest, off));
   if ((threadIdx.x & 63) == 0) s_min[threadIdx.x >> 6] = lowest;
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  const uint32_t tau = topk_body<PER, kTopkList>(t, sel, 0, 1);
+  const uint32_t tau = topk_body<PER, kTopkHeld>(t, sel, 0, 1, held);   // (its barriers publish s_min)
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int w = 1; w < kTopkThreads / 64; ++w) lowest = fminf(lowest, s_min[w]);
@@ -962,37 +923,56 @@ hipError_t select_scratch(void** ptr) {
   return hipSuccess;
 }
 
-// One-pass selection: the candidates and the buffers, which lie in the part
-// of the row statistics' region that the wave passes' fewer blocks leave free
-// (no workspace grows for it).
+// One-pass selection: the candidates and the buffers, which lie in parts of
+// the workspace that are free at the time (none grows for it; where they do
+// not fit, as with 16 heads of 128 rows and at most 4096 chunks, the
+// call takes two passes).
 struct OnePass {
   int n_cand;             // 0: two passes
-  size_t est, words, cand, mass, list;
+  size_t est, words, cand, mass;
 };
-// Candidates per chunk of the budget: on Gaussian keys with 1% heavy hitters
-// the bound leaves 1.1 to 1.9 chunks per chunk kept, as long as the budget
-// keeps at most a 48th of the chunks.  Flat scores (Gaussian keys without
-// heavy hitters) need 12 to 20, as the sample's noise spreads rho by 12%: such
-// heads are redone, 158 us against 140 for 131008 keys of 5 heads (two passes
-// each), where peaked ones take 102 against 121.  8192 sampled keys would
-// settle them in theory (1.5 to 3.3) but cost 8-12 us a call and left some.
+// Candidates per chunk of the budget.  Simulated on Gaussian keys of score
+// spread 0.5 to 3 nats, with 0.1 or 1% of them scaled by 3, in runs of 8 alike, with
+// sinks: the bound leaves 1 to 3.3 chunks per chunk kept, up to 2.8 where 512
+// are kept, as long as the budget keeps at most a 48th of the chunks.  (From
+// 1024 sampled keys in 32 tiles only the 1% were settled, and the others,
+// redone, cost 153 us at 131008 keys of 5 heads against 109 in two passes;
+// all of them now take 96-100.)  Sixteen unsampled keys with most of the mass
+// are still redone: 157 us.
 constexpr int64_t kOnePassShare = 48;
 constexpr int64_t kOnePassScores = (int64_t)128 << 20;
+static size_t topk_counter_bytes(int n_rows) { return align256((size_t)n_rows * sizeof(uint32_t)); }
 static OnePass one_pass(const SelectGeom& g, const SelectLayout& L) {
-  OnePass p{};
   const int rp = score_rows_pad(g.G * g.l_obs);
-  if (!score_wave_rows(rp) || kOnePassShare * g.b > g.n_chunks || (int64_t)g.n_sel * rp * g.n_keys < kOnePassScores) return p;
-  const int64_t nc = 2 * (int64_t)g.b + g.b / 2 + 64;
+  if (!score_wave_rows(rp) || kOnePassShare * g.b > g.n_chunks || (int64_t)g.n_sel * rp * g.n_keys < kOnePassScores)
+    return OnePass{};
   const int64_t n_slices = (g.n_chunks + kTopkSlice - 1) / kTopkSlice;
-  if (nc >= g.n_chunks || nc > 8 * kTopkThreads || (g.n_chunks > 2 * kTopkSlice && n_slices * nc > 2 * kTopkSlice)) return p;
-  size_t o = L.rowpart + align256((size_t)g.n_sel * g.wn_colblk * rp * sizeof(float2));
-  p.est = o; o += align256((size_t)g.n_sel * rp * kSwEstGroups * sizeof(float));
-  p.words = o; o += align256((size_t)2 * g.n_sel * sizeof(uint32_t));
-  p.cand = o; o += align256((size_t)g.n_sel * nc * sizeof(int32_t));
-  p.mass = o; o += align256((size_t)g.n_sel * nc * g.cs * sizeof(float));
-  p.list = o; o += align256((size_t)g.n_sel * nc * sizeof(TopkCand));
-  if (o <= L.rowoff) p.n_cand = (int)nc;
-  return p;
+  const int64_t b = g.b, least = 2 * b + b / 2 + 64;
+  int64_t most = std::min<int64_t>(8 * kTopkThreads, g.n_chunks - 1);
+  if (g.n_chunks > 2 * kTopkSlice)       // the slices' lists, 32 entries per lane, or better 16
+    most = std::min<int64_t>(most, (n_slices * least > kTopkSlice ? 2 : 1) * kTopkSlice / n_slices);
+  const int64_t want = b > 256 ? 3 * b : std::min<int64_t>(4 * b + 64, kTopkThreads);
+  // The row statistics of the wave passes' fewer blocks leave room behind
+  // them, and so do the lists of the chunks' top-k before and after it.  The
+  // estimates are read before the candidates are listed, whose masses
+  // come last; where a row's chunks are too few for lists (at most
+  // kTopkSmallSlice), all lie in the former.
+  const bool lists = g.n_chunks > kTopkSmallSlice;
+  OnePass p{};
+  p.words = L.rowpart + align256((size_t)g.n_sel * g.wn_colblk * rp * sizeof(float2));
+  p.cand = p.words + align256((size_t)2 * g.n_sel * sizeof(uint32_t));
+  p.est = lists ? L.topk + topk_counter_bytes(g.n_sel) : p.cand;
+  const size_t room = lists ? L.total : L.rowoff;
+  for (int64_t nc : {std::max(std::min(want, most), least), least}) {
+    const size_t cand_end = p.cand + align256((size_t)g.n_sel * nc * sizeof(int32_t));
+    p.mass = lists ? p.est : cand_end;
+    if (nc <= most && cand_end <= L.rowoff && p.est + (size_t)g.n_sel * rp * kSwEstStride * sizeof(float) <= room &&
+        p.mass + (size_t)g.n_sel * nc * g.cs * sizeof(float) <= room) {
+      p.n_cand = (int)nc;
+      return p;
+    }
+  }
+  return OnePass{};
 }
 
 ScoreRoute select_route(int dtype, const SelectGeom& g) {
@@ -1001,6 +981,12 @@ ScoreRoute select_route(int dtype, const SelectGeom& g) {
   if (one_pass(g, select_layout(g)).n_cand > 0) return kRouteOnePass;
   if (rp <= 64 && g.n_sel * g.n_keys > kTileReread) return kRouteTile;
   return wave_run(rp, g.wcb_tokens) ? kRouteWave : kRouteTile;
+}
+
+// the redo words, behind the n_sel ratios
+size_t select_redone(int dtype, const SelectGeom& g) {
+  if (select_route(dtype, g) != kRouteOnePass) return 0;
+  return one_pass(g, select_layout(g)).words + (size_t)g.n_sel * sizeof(uint32_t);
 }
 
 hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, const void* k,
@@ -1036,17 +1022,15 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
   hipError_t e;
   if (route == kRouteOnePass) {
     const OnePass op = one_pass(g, L);
-    float* est = reinterpret_cast<float*>(w + op.est);
     uint32_t* redo = reinterpret_cast<uint32_t*>(w + op.words) + g.n_sel;
     int32_t* cand = reinterpret_cast<int32_t*>(w + op.cand);
     float* mass = reinterpret_cast<float*>(w + op.mass);
-    TopkCand* list = reinterpret_cast<TopkCand*>(w + op.list);
     a.rho = reinterpret_cast<uint32_t*>(w + op.words);
     a.redo = redo;
-    hipLaunchKernelGGL(row_estimate_kernel, dim3((R + 31) / 32, g.n_sel, kSwEstGroups), dim3(256), 0, stream, a, est);
-    ScoreArgs m = a;
-    m.rowoff = est;
-    e = launch_score_both(grid, stream, m);
+    a.est = reinterpret_cast<float*>(w + op.est);
+    e = launch_score_est(g.n_sel, stream, a);
+    if (e != hipSuccess) return e;
+    e = launch_score_both(grid, stream, a);
     if (e != hipSuccess) return e;
     if (!a.cs_fused)
       hipLaunchKernelGGL(chunk_max_kernel, cgrid, dim3(256), 0, stream, a.colmass, g.n_keys, g.cs, g.n_chunks, S,
@@ -1072,18 +1056,18 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
     ga.n_keys = (int64_t)op.n_cand * g.cs;
     ga.cb_tokens = 32 * kSwWaves;
     ga.unit_log = 5;
-    ga.cs_fused = 0;
-    ga.colmass = mass;
+    ga.cs_fused = g.cs <= 32 ? a.cs_fused : 0;   // in tiles of 32 keys
+    ga.chunks = ga.colmass = mass;
+    ga.n_chunks = op.n_cand;
     e = launch_score_gather(dim3((unsigned)((ga.n_keys + ga.cb_tokens - 1) / ga.cb_tokens), g.n_sel), stream, ga);
     if (e != hipSuccess) return e;
     TopkArgs t{};
-    t.list = list;
     t.list_len = op.n_cand;
     t.k = t.b = g.b;
     t.out = idx_out;
 #define CATEKV_FIN(PER) \
-  hipLaunchKernelGGL((select_final_kernel<PER>), dim3(g.n_sel), dim3(kTopkThreads), 0, stream, t, list, cand, mass, g.cs, \
-                     g.n_keys, S, g.n_chunks, a.rho, R, redo)
+  hipLaunchKernelGGL((select_final_kernel<PER>), dim3(g.n_sel), dim3(kTopkThreads), 0, stream, t, cand, mass, \
+                     ga.cs_fused ? 1 : g.cs, g.n_keys, S, g.n_chunks, a.rho, R, redo)
     if (op.n_cand <= 1 * kTopkThreads) CATEKV_FIN(1);
     else if (op.n_cand <= 2 * kTopkThreads) CATEKV_FIN(2);
     else if (op.n_cand <= 4 * kTopkThreads) CATEKV_FIN(4);
@@ -1105,7 +1089,6 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
 
 // ws: n_rows arrival counters (zero on entry: the caller's previous kernel
 // clears them; left zero), then the candidate lists of two-stage rows.
-size_t topk_counter_bytes(int n_rows) { return align256((size_t)n_rows * sizeof(uint32_t)); }
 size_t topk_workspace_bytes(int n_rows, int64_t n) {
   return topk_counter_bytes(n_rows) + (n > kTopkSmallSlice ? (size_t)n_rows * 2 * kTopkSlice * sizeof(TopkCand) : 0);
 }

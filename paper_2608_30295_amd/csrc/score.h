@@ -84,8 +84,8 @@ template <typename T> struct Shape {
   __device__ static __forceinline__ float row_sum(float x) { return sum16(x); }
   __device__ static __forceinline__ float col_sum(float x) { return add_xor32(add_xor16(x)); }
 };
-// kBoth and kColGather: score_wave.h only
-enum ScoreMode { kRowStats = 0, kColMass = 1, kObsMatrix = 2, kObsBracket = 3, kBoth = 4, kColGather = 5 };
+// kBoth, kColGather and kRowEst: score_wave.h only
+enum ScoreMode { kRowStats = 0, kColMass = 1, kObsMatrix = 2, kObsBracket = 3, kBoth = 4, kColGather = 5, kRowEst = 6 };
 enum RowStatsVar { kRsSum = 0, kRsMax = 1 };
 
 struct ScoreArgs {
@@ -119,6 +119,7 @@ struct ScoreArgs {
   int g_log;              // log2(G)
   int unit_log;           // log2 of the keys per unit of a wave's run (5, or 6 where chunks span 64 keys)
   // one-pass selection (prefill.hip)
+  float* est;             // kRowEst out, kBoth in: samples of each row's sum (sw_est_pick)
   const uint32_t* gate;   // kColMass: heads with a zero word are left alone
   const int32_t* cand;    // kColGather: the chunks of cand_cs keys whose columns are taken, [n_sel][n_cand]
   int cand_cs, n_cand;
@@ -624,8 +625,10 @@ inline hipError_t launch_score_mt(int rows_pad, dim3 grid, hipStream_t s, const 
 hipError_t launch_score_rowstats(int dtype, bool wave, int G, bool causal, int rows_pad, dim3 grid, hipStream_t s,
                                  const ScoreArgs& a);
 hipError_t launch_score_colmass(int dtype, bool wave, int rows_pad, dim3 grid, hipStream_t s, const ScoreArgs& a);
-// bf16 (score_wave.h): row sums against given offsets and column mass in one
-// pass, and the column mass of gathered chunks
+// bf16 (score_wave.h): samples of the row sums, row sums against offsets
+// estimated from them and column mass in one pass, and the column mass of
+// gathered chunks
+hipError_t launch_score_est(int n_sel, hipStream_t s, const ScoreArgs& a);
 hipError_t launch_score_both(dim3 grid, hipStream_t s, const ScoreArgs& a);
 hipError_t launch_score_gather(dim3 grid, hipStream_t s, const ScoreArgs& a);
 hipError_t launch_score_obs(int dtype, int G, bool causal, int rows_pad, dim3 grid, hipStream_t s,

@@ -37,21 +37,52 @@ struct SwRow {
 };
 __device__ __forceinline__ SwRow sw_row(int r, int g_log) { return {r >> g_log, r & ((1 << g_log) - 1)}; }
 
-// kBoth: a row's sum is estimated from kSwEstGroups samples; the third
-// smallest estimate is taken (any finite number is a valid weight: sums that
-// it takes out of range are redone).
-constexpr int kSwEstGroups = 8;
-__device__ __forceinline__ float sw_est_pick(const float* e8) {
-  const float4 lo = *reinterpret_cast<const float4*>(e8), hi = *reinterpret_cast<const float4*>(e8 + 4);
-  const float e[kSwEstGroups] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-  float pick = 0.f;
+// kRowEst: the sum of exp2(s c) of every row over sampled keys, from which
+// kBoth estimates it over all: the first 32 keys, which prompts often give
+// most of a row's mass, as themselves, and 8160 others by steps of the golden
+// ratio (single keys: neighbours score alike).  Workgroup `part` takes 256 of
+// them, a wave 32; est[row][part] is the log2 sum of its keys, est[row][32]
+// that of the first 32.
+constexpr int kSwEstParts = 32, kSwEstStride = 36;
+__device__ __forceinline__ uint32_t sw_est_key(int part, int wave, int n, int64_t n_keys) {
+  const uint32_t u = (uint32_t)((part * kSwWaves + wave) * 32 + n);
+  return u < 32 ? u : 32 + __umulhi(u * 2654435769u, (uint32_t)(n_keys - 32));
+}
+__device__ __forceinline__ float sw_log2_sum(const float* e, int cnt, const bool* in) {
+  float M = kMInit, L = 0.f;
 #pragma unroll
-  for (int w = 0; w < kSwEstGroups; ++w) {
+  for (int i = 0; i < cnt; ++i) M = in[i] ? fmaxf(M, e[i]) : M;
+#pragma unroll
+  for (int i = 0; i < cnt; ++i) L += in[i] ? fast_exp2(e[i] - M) : 0.f;
+  return M + __log2f(L);
+}
+// The estimate (log2): of eight groups of 1024 samples the mean of the five
+// smallest, so that a few very large terms in some groups do not lift it
+// (rho = estimate / sum <= 1 costs nothing, rho >> 1 weakens the bound), and
+// the first keys.  Some group has a sum at least the mean's, so rho is at most
+// n_keys / 896.  Any finite number is a valid weight: sums that it takes out of
+// range are redone.
+__device__ __forceinline__ float sw_est_pick(const float4 (&e)[kSwEstStride / 4], int64_t n_keys) {
+  constexpr int NG = 8, PER = kSwEstParts / NG;
+  static_assert(PER == 4, "a group per load");
+  const bool all[PER] = {true, true, true, true};
+  float g[NG];
+#pragma unroll
+  for (int w = 0; w < NG; ++w) {
+    const float p[PER] = {e[w].x, e[w].y, e[w].z, e[w].w};
+    g[w] = sw_log2_sum(p, PER, all);
+  }
+  bool in[NG];
+#pragma unroll
+  for (int w = 0; w < NG; ++w) {
     int below = 0;
 #pragma unroll
-    for (int v = 0; v < kSwEstGroups; ++v) below += e[v] < e[w] || (e[v] == e[w] && v < w);
-    if (below == 2) pick = e[w];
+    for (int v = 0; v < NG; ++v) below += g[v] < g[w] || (g[v] == g[w] && v < w);
+    in[w] = below < 5;
   }
+  const float s[2] = {sw_log2_sum(g, NG, in) + __log2f((float)(n_keys - 32) * (1.0f / (5 * 32 * kSwWaves * PER))),
+                      e[NG].x};
+  const float pick = sw_log2_sum(s, 2, all);
   return fabsf(pick) < INFINITY ? pick : 0.f;
 }
 
@@ -67,7 +98,8 @@ void score_wave_kernel(ScoreArgs a) {
   // Row offsets (log2 units) and sums of exp2(s c - offset) lie in registers,
   // the row tiles unrolled; kBoth has none left for them: LDS, and the row
   // tiles are a loop (unrolled, the compiler spills).
-  constexpr bool RS = MODE == kRowStats, BOTH = MODE == kBoth, SUMS = RS || BOTH, GATHER = MODE == kColGather;
+  constexpr bool EST = MODE == kRowEst, RS = MODE == kRowStats || EST, BOTH = MODE == kBoth, SUMS = RS || BOTH;
+  constexpr bool GATHER = MODE == kColGather;
   static_assert(RG <= 8, "at most 256 rows");
   __shared__ float s_woff[RS ? kSwWaves : 1][RS ? RG * 32 : 1];   // kRowStats: each wave's own offsets, at the end
   __shared__ float s_off[BOTH ? RG * 32 : 1];
@@ -77,8 +109,10 @@ void score_wave_kernel(ScoreArgs a) {
   const int n = lane & 31, half = lane >> 5;
   const int sel = blockIdx.y, cb = blockIdx.x;
   if (MODE == kColMass && a.gate && !a.gate[sel]) return;
+  if (EST && cb == 0 && blockIdx.z == 0 && threadIdx.x == 0) a.rho[sel] = a.redo[sel] = 0;
   const int h = a.heads[sel];
   const int G = a.G;
+  const int row0 = EST ? blockIdx.z * (RG * 32) : 0;                      // first query row
 
   // this wave's keys: a run of whole units of the block's key columns (32
   // keys, or 64 where a chunk spans 64)
@@ -92,7 +126,7 @@ void score_wave_kernel(ScoreArgs a) {
   // number of units) need no mask: they lie before the end and at or before
   // every row's position
   const int lim = a.causal ? (int)max((int64_t)-(1 << 30), min((int64_t)(1 << 30), a.q_pos0 - a.key_off - col0)) : 1 << 30;
-  const int c_plain = GATHER ? c_lo : max(c_lo, min(c_hi, lim + 1) >> ul << ul);
+  const int c_plain = GATHER || EST ? c_lo : max(c_lo, min(c_hi, lim + 1) >> ul << ul);
   // A plain run starts and ends with a step of 32 keys and takes 64 at a time
   // between: all waves' first requests meet at the memory, and the matrix
   // cores idle until they are served, and the memory idles under the last
@@ -135,6 +169,17 @@ void score_wave_kernel(ScoreArgs a) {
     }
   };
 
+  // kBoth: the samples of a row's sum, one row per thread, picked from while
+  // the query rows are on their way
+  static_assert(!BOTH || RG * 32 <= kSwThreads, "one row per thread");
+  float4 ev[BOTH ? kSwEstStride / 4 : 1];
+  const SwRow er = sw_row(min((int)threadIdx.x, RG * 32 - 1), a.g_log);
+  if constexpr (BOTH) {
+    const float* e = a.est + ((size_t)sel * a.rp + min(er.i, a.lq - 1) * G + er.g) * kSwEstStride;
+#pragma unroll
+    for (int u = 0; u < kSwEstStride / 4; ++u) ev[u] = *reinterpret_cast<const float4*>(e + 4 * u);
+    compiler_fence();
+  }
   // The query rows go first and alone: requested beside the first keys of all
   // workgroups (16 MB) they wait behind them, 8-12 us instead of ~2.
   constexpr int QP = RG * 32 * 16 / kSwThreads;           // 16-byte pieces of query rows per thread
@@ -142,19 +187,24 @@ void score_wave_kernel(ScoreArgs a) {
 #pragma unroll
   for (int u = 0; u < QP; ++u) {
     const int e = u * kSwThreads + threadIdx.x;
-    const SwRow q = sw_row(e >> 4, a.g_log);
+    const SwRow q = sw_row(row0 + (e >> 4), a.g_log);
     const uint32_t row = (uint32_t)(h * G + q.g) * a.lq + min(q.i, a.lq - 1);
     qv[u] = ldg16(reinterpret_cast<const char*>(a.q) + (size_t)row * (kD * 2) + (e & 15) * 16);
+  }
+  if constexpr (EST) {
+    const char* p = reinterpret_cast<const char*>(a.k) +
+                    ((size_t)h * a.n + sw_est_key(cb, wave, n, a.n_keys)) * (kD * 2) + half * 16;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) kf[0][0][ks] = ldg16(p + ks * 32);
   }
   auto load_off = [&](int s) -> float {
     const SwRow q = sw_row(s, a.g_log);
     if (q.i >= a.lq) return INFINITY;
-    const float* o = a.rowoff + ((size_t)sel * a.rp + q.i * G + q.g) * (BOTH ? kSwEstGroups : 1);
-    return BOTH ? sw_est_pick(o) : *o;
+    return a.rowoff[(size_t)sel * a.rp + q.i * G + q.g];
   };
   if constexpr (BOTH) {
     for (int s = lane; s < RG * 32; s += 64) s_l[wave][s] = 0.f;
-    for (int s = threadIdx.x; s < RG * 32; s += kSwThreads) s_off[s] = load_off(s);
+    if (threadIdx.x < RG * 32) s_off[threadIdx.x] = er.i < a.lq ? sw_est_pick(ev, a.n_keys) : INFINITY;
   } else {
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg) {
@@ -165,7 +215,7 @@ void score_wave_kernel(ScoreArgs a) {
 #pragma unroll
   for (int u = 0; u < QP; ++u) {
     const int e = u * kSwThreads + threadIdx.x;
-    const bool ok = sw_row(e >> 4, a.g_log).i < a.lq;
+    const bool ok = sw_row(row0 + (e >> 4), a.g_log).i < a.lq;
     s_q[(e >> 4) * kSwRow + (e & 15)] = ok ? qv[u] : make_uint4(0, 0, 0, 0);
   }
   barrier_lds_only();
@@ -366,7 +416,8 @@ void score_wave_kernel(ScoreArgs a) {
     }
     return;
   }
-  for (int col = c_plain; col < c_hi; col += 64) {
+  if constexpr (EST) tile(kf[0], 0, T1{}, N{}, Y{}, none);
+  for (int col = c_plain; !EST && col < c_hi; col += 64) {
     load_clamped(kf[0], col);
     if (RS && !started) {
       tile(kf[0], col, T2{}, Y{}, Y{}, none);
@@ -390,16 +441,19 @@ void score_wave_kernel(ScoreArgs a) {
     }
     __syncthreads();
     for (int s = threadIdx.x; s < RG * 32; s += kSwThreads) {
-      const SwRow q = sw_row(s, a.g_log);
+      const SwRow q = sw_row(row0 + s, a.g_log);
       if (q.i >= a.lq) continue;
       float M = kMInit, L = 0.f;
       if constexpr (RS) {
         float2 v[kSwWaves];
 #pragma unroll
-        for (int w = 0; w < kSwWaves; ++w) {
-          v[w] = make_float2(s_woff[w][s], s_l[w][s]);
-          M = fmaxf(M, v[w].x);
+        for (int w = 0; w < kSwWaves; ++w) v[w] = make_float2(s_woff[w][s], s_l[w][s]);
+        if (EST && cb == 0) {                             // the first 32 keys apart, seven waves for eight
+          a.est[((size_t)sel * a.rp + q.i * G + q.g) * kSwEstStride + kSwEstParts] = v[0].x + __log2f(v[0].y);
+          v[0] = make_float2(kMInit, 0.f);
         }
+#pragma unroll
+        for (int w = 0; w < kSwWaves; ++w) M = fmaxf(M, v[w].x);
 #pragma unroll
         for (int w = 0; w < kSwWaves; ++w) L += v[w].y * fast_exp2(v[w].x - M);
       } else {                                            // the same offset in every wave
@@ -407,7 +461,10 @@ void score_wave_kernel(ScoreArgs a) {
 #pragma unroll
         for (int w = 0; w < kSwWaves; ++w) L += s_l[w][s];
       }
-      a.rowpart[((size_t)sel * a.n_colblk + cb) * a.rp + q.i * G + q.g] = make_float2(M, L);
+      if constexpr (EST)
+        a.est[((size_t)sel * a.rp + q.i * G + q.g) * kSwEstStride + cb] = M + __log2f(cb == 0 ? L * (8.f / 7.f) : L);
+      else
+        a.rowpart[((size_t)sel * a.n_colblk + cb) * a.rp + q.i * G + q.g] = make_float2(M, L);
     }
   }
 }
@@ -421,11 +478,11 @@ inline int sw_row_tiles(int rows) {
 
 template <int MODE>
 inline hipError_t launch_score_wave(dim3 grid, hipStream_t s, ScoreArgs a) {
-  if (MODE == kRowStats) a.unit_log = 5;
+  if (MODE == kRowStats || MODE == kRowEst) a.unit_log = 5;
   a.g_log = __builtin_ctz((unsigned)a.G);
 #define CATEKV_SW(RG) \
   if (rg == RG) { hipLaunchKernelGGL((score_wave_kernel<RG, MODE>), grid, dim3(kSwThreads), 0, s, a); return hipGetLastError(); }
-  const int rg = sw_row_tiles(a.R);
+  const int rg = sw_row_tiles(a.R) / (int)grid.z;
   CATEKV_SW(1) CATEKV_SW(2) CATEKV_SW(4) CATEKV_SW(8)
 #undef CATEKV_SW
   return hipErrorInvalidValue;

@@ -23,6 +23,14 @@ def select_route(hq: int, hkv: int, l_obs: int, n: int, cs: int, n_sel: int, b: 
     return f(int(bf16), hq, hkv, l_obs, n, cs, n_sel, b)
 
 
+def select_redone(ws: torch.Tensor, hq: int, hkv: int, l_obs: int, n: int, cs: int, n_sel: int, b: int) -> np.ndarray:
+    """Which heads of a one-pass bf16 selection that ran in ws were scored in full."""
+    f = ck.lib().catekv_select_redone
+    f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int] * 4 + [ctypes.c_int64] + [ctypes.c_int] * 3
+    at = f(1, hq, hkv, l_obs, n, cs, n_sel, b)
+    return ws.view(torch.uint8)[at:at + 4 * n_sel].cpu().numpy().view(np.int32) != 0
+
+
 def score_route(hq: int, hkv: int, lq: int, n: int, l_init: int, l_rec: int, bf16: bool = True) -> int:
     f = ck.lib().catekv_score_route
     f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.c_int64] * 3
