@@ -397,6 +397,11 @@ size_t catekv_select_redone(int dtype, int hq, int hkv, int l_obs, int64_t n, in
 int catekv_score_route(int dtype, int hq, int hkv, int lq, int64_t n, int64_t l_init, int64_t l_rec) {
   return catekv::score_route(dtype, score_geom(hq, hkv, lq, n, l_init, l_rec));
 }
+// Workgroups per head of the launch that lists the bracket's entries, or takes
+// the radix route's first pass over A.
+int catekv_score_list_blocks(int dtype, int hq, int hkv, int lq, int64_t n, int64_t l_init, int64_t l_rec) {
+  return (int)catekv::score_list_blocks(dtype, score_geom(hq, hkv, lq, n, l_init, l_rec));
+}
 
 int catekv_compact_kv(int dtype, const void* k, const void* v, int hkv, int64_t n, int d, int cs,
                       int l_obs, const int32_t* sel_heads_host, int n_sel, const int32_t* idx, int b,

@@ -772,6 +772,18 @@ hipError_t launch_cv_sample(const ScoreArgs& a, double k_pct, double alpha, hipS
   return hipGetLastError();
 }
 
+// radix-route passes over A: 128 workgroups per head (launches that only
+// return on the bracket route stay short)
+static unsigned radix_blocks(int64_t N) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(128, (N + 1023) / 1024)); }
+// The listing launch: two workgroups per column block, which hold all its
+// buffers (at most kCvMaxSub) and spread the radix route's first pass over
+// the device where there are few heads: one workgroup per kRegions buffers,
+// a fourth of those at four waves per block, took 210 us for two heads of
+// 32 x 937766, this 76.
+unsigned cv_list_blocks(int64_t N, int n_colblk) {
+  return (unsigned)std::max<int64_t>(radix_blocks(N), (int64_t)n_colblk * (kCvMaxSub / kRegions));
+}
+
 hipError_t launch_cv_finish(const ScoreArgs& a, double k_pct, double alpha, float* cv_out, hipStream_t stream) {
   const int hkv = a.hkv, lq = a.lq;
   const int64_t n_keys = a.n_keys, N = (int64_t)lq * n_keys;
@@ -780,10 +792,8 @@ hipError_t launch_cv_finish(const ScoreArgs& a, double k_pct, double alpha, floa
   uint32_t* hist = c.hist;
   const float* A = a.obs;
   const int nbuf = a.n_colblk * c.nsub;
-  // radix-route passes over A: 128 workgroups per head (launches that only
-  // return on the bracket route stay short)
-  const unsigned hb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(128, (N + 1023) / 1024));
-  const unsigned lw = (unsigned)std::max<int64_t>(hb, (nbuf + kRegions - 1) / kRegions);
+  const unsigned hb = radix_blocks(N);
+  const unsigned lw = cv_list_blocks(N, a.n_colblk);
   const dim3 walk((unsigned)col_blocks(n_keys, hkv), hkv), flat(hb, hkv);
   hipLaunchKernelGGL(cv_list_kernel, dim3(lw, hkv), dim3(256), 0, stream, A, N, c.st, hist, hist + hs, c.pairs,
                      c.pfill, c.capw, nbuf, c.list, k_pct, alpha);

@@ -170,6 +170,7 @@ struct ScoreGeom {
 
 size_t score_workspace_bytes(const ScoreGeom& g);
 ScoreRoute score_route(int dtype, const ScoreGeom& g);   // of the row statistics
+unsigned score_list_blocks(int dtype, const ScoreGeom& g);   // workgroups per head of the listing launch
 
 hipError_t launch_score(int dtype, const ScoreGeom& g, const void* q_rows, const void* k,
                         float* cv_out, void* ws, hipStream_t stream);

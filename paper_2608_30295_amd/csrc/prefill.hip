@@ -1206,6 +1206,10 @@ ScoreRoute score_route(int dtype, const ScoreGeom& g) {
   return dtype == CATEKV_BF16 && wave_run(rp, g.wcb_tokens) ? kRouteWave : kRouteTile;
 }
 
+unsigned score_list_blocks(int dtype, const ScoreGeom& g) {
+  return cv_list_blocks((int64_t)g.lq * g.n_keys, dtype == CATEKV_BF16 ? g.n_colblk : g.fn_colblk);
+}
+
 hipError_t launch_score(int dtype, const ScoreGeom& g, const void* q_rows, const void* k,
                         float* cv_out, void* ws, hipStream_t stream) {
   const ScoreLayout L = score_layout(g);

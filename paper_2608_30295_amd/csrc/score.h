@@ -641,6 +641,7 @@ hipError_t launch_score_obs_bracket(int dtype, int G, bool causal, int rows_pad,
 // the bracketing pass the order statistic, the column counts and the score.
 size_t cv_workspace_bytes(int hkv, int lq, int64_t n_keys, int n_colblk);
 CvLink cv_link(void* ws, int hkv, int lq, int64_t n_keys, int n_colblk, int nsub);
+unsigned cv_list_blocks(int64_t N, int n_colblk);
 hipError_t launch_cv_sample(const ScoreArgs& a, double k_pct, double alpha, hipStream_t s);
 hipError_t launch_cv_finish(const ScoreArgs& a, double k_pct, double alpha, float* cv_out, hipStream_t s);
 

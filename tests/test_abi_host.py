@@ -296,3 +296,16 @@ def test_fp32_blocks_fill_one_round(rows, n_sel):
         elif tiles <= 4 * per_head:
             assert blocks <= per_head, (n_keys, blocks)              # one round
         assert blocks * 4 >= min(tiles, per_head), (n_keys, blocks)
+
+
+@pytest.mark.parametrize("hkv", [1, 2, 4, 8])
+@pytest.mark.parametrize("group,lq", [(1, 32), (1, 64), (4, 64), (8, 64)])
+def test_listing_launch_fills_the_device(hkv, group, lq):
+    """The launch that lists the bracket's entries also makes the radix
+    route's first pass over the observation matrix: whatever the number of
+    heads, about two workgroups per compute unit (one where a column block has
+    one to itself)."""
+    f = ck.lib().catekv_score_list_blocks
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.c_int64] * 3
+    for bf16 in (0, 1):
+        assert hkv * f(bf16, hkv * group, hkv, lq, 500000, 64, 16) >= 500
