@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("hkv,G,lq,n,scale,dtype", [
-    (64, 1, 16, 135000 + 37, 1.0, torch.bfloat16),     # blocks of 16887 columns: two counting windows
+    (64, 1, 16, 135000 + 37, 1.0, torch.bfloat16),     # blocks of 16896 columns on 256 compute units: two counting windows
+    (64, 1, 16, 190000 + 37, 1.0, torch.bfloat16),     # 23808: well beyond the first window's 16384
     (32, 2, 33, 70001, 1.0, torch.bfloat16),
     (8, 4, 16, 30011, 0.02, torch.bfloat16),           # near-uniform rows
     (64, 1, 8, 20005, 1.0, torch.float32),
