@@ -236,6 +236,7 @@ catekv::SelectGeom select_geom(int hq, int hkv, int l_obs, int64_t n, int cs, co
   g.unit_log = cs == 64 ? 6 : 5;   // a chunk fused into the pass never spans two units' waves
   g.wcb_tokens = catekv::score_wave_block_tokens(g.n_keys, n_sel, g.unit_log, device_cus());
   g.wn_colblk = (int)((std::max<int64_t>(g.n_keys, 1) + g.wcb_tokens - 1) / g.wcb_tokens);
+  g.n_cu = std::max(1, device_cus());
   for (int i = 0; i < n_sel && heads; ++i) g.heads[i] = heads[i];
   return g;
 }

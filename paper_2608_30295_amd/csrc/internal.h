@@ -95,6 +95,7 @@ struct SelectGeom {
   int wn_colblk, unit_log;
   int64_t fcb_tokens;      // the same of the fp32 passes
   int fn_colblk;
+  int n_cu;                // compute units
   int heads[128];
 };
 

@@ -933,8 +933,9 @@ struct OnePass {
 };
 // Candidates per chunk of the budget.  Simulated on Gaussian keys of score
 // spread 0.5 to 3 nats, with 0.1 or 1% of them scaled by 3, in runs of 8 alike, with
-// sinks: the bound leaves 1 to 3.3 chunks per chunk kept, up to 2.8 where 512
-// are kept, as long as the budget keeps at most a 48th of the chunks.  (From
+// sinks: the bound leaves 1 to 3.3 chunks per chunk kept, as long as the budget
+// keeps at most a 48th of the chunks; four are taken.  (With 2.6 some heads of
+// 1M keys without heavy hitters, or with sinks, were redone: 866 against 575 us.  From
 // 1024 sampled keys in 32 tiles only the 1% were settled, and the others,
 // redone, cost 153 us at 131008 keys of 5 heads against 109 in two passes;
 // all of them now take 96-100.)  Sixteen unsampled keys with most of the mass
@@ -949,9 +950,11 @@ static OnePass one_pass(const SelectGeom& g, const SelectLayout& L) {
   const int64_t n_slices = (g.n_chunks + kTopkSlice - 1) / kTopkSlice;
   const int64_t b = g.b, least = 2 * b + b / 2 + 64;
   int64_t most = std::min<int64_t>(8 * kTopkThreads, g.n_chunks - 1);
-  if (g.n_chunks > 2 * kTopkSlice)       // the slices' lists, 32 entries per lane, or better 16
-    most = std::min<int64_t>(most, (n_slices * least > kTopkSlice ? 2 : 1) * kTopkSlice / n_slices);
-  const int64_t want = b > 256 ? 3 * b : std::min<int64_t>(4 * b + 64, kTopkThreads);
+  if (g.n_chunks > 2 * kTopkSlice) {     // the slices' lists: 32 entries per lane, or 16 where those hold nearly 3 b
+    const int64_t per = kTopkSlice / n_slices;
+    most = std::min<int64_t>(most, 8 * per >= 23 * b && per >= least ? per : 2 * per);
+  }
+  const int64_t want = std::max(4 * b, std::min<int64_t>(4 * b + 64, kTopkThreads));
   // The row statistics of the wave passes' fewer blocks leave room behind
   // them, and so do the lists of the chunks' top-k before and after it.  The
   // estimates are read before the candidates are listed, whose masses
@@ -1054,7 +1057,10 @@ hipError_t launch_select(int dtype, const SelectGeom& g, const void* q_obs, cons
     ga.n_cand = op.n_cand;
     ga.cand_keys = g.n_keys;
     ga.n_keys = (int64_t)op.n_cand * g.cs;
-    ga.cb_tokens = 32 * kSwWaves;
+    // one round of workgroups, a tile or more per wave (6 heads, 2048 candidates
+    // of 8 keys, the next tile ahead: 21.0 -> 19.0 us)
+    const int64_t per_head = std::max(1, g.n_cu / g.n_sel) * (int64_t)(32 * kSwWaves);
+    ga.cb_tokens = std::min<int64_t>((ga.n_keys + per_head - 1) / per_head, 64) * (32 * kSwWaves);
     ga.unit_log = 5;
     ga.cs_fused = g.cs <= 32 ? a.cs_fused : 0;   // in tiles of 32 keys
     ga.chunks = ga.colmass = mass;

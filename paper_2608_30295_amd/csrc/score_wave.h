@@ -191,6 +191,14 @@ void score_wave_kernel(ScoreArgs a) {
     const uint32_t row = (uint32_t)(h * G + q.g) * a.lq + min(q.i, a.lq - 1);
     qv[u] = ldg16(reinterpret_cast<const char*>(a.q) + (size_t)row * (kD * 2) + (e & 15) * 16);
   }
+  // kColGather: 32 gathered keys from column col; past the block's end its last one again
+  auto load_gathered = [&](uint4 (&f)[KS], int col) {
+    const uint32_t x = min(col + n, n_cols - 1) + (uint32_t)col0, cs = (uint32_t)a.cand_cs;
+    const int64_t key = min((int64_t)a.cand[(size_t)sel * a.n_cand + x / cs] * cs + x % cs, a.cand_keys - 1);
+    const char* p = reinterpret_cast<const char*>(a.k) + ((size_t)h * a.n + (size_t)key) * (kD * 2) + half * 16;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) f[ks] = ldg16(p + ks * 32);
+  };
   if constexpr (EST) {
     const char* p = reinterpret_cast<const char*>(a.k) +
                     ((size_t)h * a.n + sw_est_key(cb, wave, n, a.n_keys)) * (kD * 2) + half * 16;
@@ -406,13 +414,12 @@ void score_wave_kernel(ScoreArgs a) {
   }
   bool started = pu > 0;                    // kRowStats: offsets taken
   if constexpr (GATHER) {                   // 32 gathered keys at a time
+    if (c_lo < c_hi) load_gathered(kf[0][0], c_lo);
     for (int col = c_lo; col < c_hi; col += 32) {
-      const uint32_t x = min(col + n, n_cols - 1) + (uint32_t)col0, cs = (uint32_t)a.cand_cs;
-      const int64_t key = min((int64_t)a.cand[(size_t)sel * a.n_cand + x / cs] * cs + x % cs, a.cand_keys - 1);
-      const char* p = reinterpret_cast<const char*>(a.k) + ((size_t)h * a.n + (size_t)key) * (kD * 2) + half * 16;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kf[0][0][ks] = ldg16(p + ks * 32);
+      if (col + 32 < c_hi) load_gathered(kf[1][0], col + 32);
       tile(kf[0], col, T1{}, N{}, N{}, none);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[0][0][ks] = kf[1][0][ks];
     }
     return;
   }
